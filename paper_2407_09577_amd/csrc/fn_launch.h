@@ -64,6 +64,15 @@ struct PrefillArgs {
 };
 hipError_t launch_prefill_bf16(const PrefillArgs& p);
 
+// Middle rows (mid_bf16.hip): the workgroup shape for a call without a forced tile, or -1 when
+// the many-row tiles are to take it.  Every kind but the per-head norms, no run-time g.
+constexpr int kMidMaxM = 1536;
+int mid_shape(int M, int K, int NP, bool glu);
+hipError_t launch_mid_bf16(const PrefillArgs& p, int shape);
+// Estimated time of the many-row kernel's automatic tiles, us on MI355X.
+float prefill_estimate_us(int M, int K, int NP, bool glu);
+float estimate_us(float r, int K, float fix, float round, float fill);
+
 struct DecodeArgs {
   const __bf16* a;
   int M, K, lda;

@@ -1,0 +1,91 @@
+// Middle rows: which workgroup shape of mid_kernel.h a call takes, or none (the many-row
+// tiles).  The kinds are instantiated in mid_kinds_*.hip.
+#include "mid_kernel.h"
+
+namespace fn {
+
+extern template hipError_t launch_mid_epi<EPI_RMS>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_GLU>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_LN>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_NONE>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_GLU_NOSCALE>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_REGLU>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_BILINEAR>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_GLU_DEFER>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_RELU_DEFER>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_ROWSCALE>(const PrefillArgs&, int);
+extern template hipError_t launch_mid_epi<EPI_ROPE>(const PrefillArgs&, int);
+
+// Workgroup shapes: 16-row blocks and packed column blocks of a workgroup, and its time in us
+// on MI355X as a function of r = workgroups / 256 (the compute units):
+//   fix max(1, r) + K / 1024 (round ceil(r) + fill min(1, r)).
+// A workgroup's time per k is constant, a round ends when its last workgroup does, and units
+// that share the memory slow each other down a little.  The constants are least-squares fits
+// over 1423 random bf16 shapes (17..1500 rows, K 512..8192, 512..20480 columns, linear and
+// GLU), each shape of the table within 5 to 18% rms.  Shapes 13..15 are 2, 5 and 8 with
+// non-temporal weight loads.
+struct MidShape {
+  int mb, blocks;
+  float fix, round, fill;
+};
+static constexpr MidShape kMidShapes[] = {
+    {2, 2, 2.34f, 1.09f, 1.41f}, {2, 4, 2.68f, 1.90f, 1.28f}, {2, 6, 2.87f, 2.82f, 1.28f},
+    {3, 2, 2.71f, 1.47f, 1.32f}, {3, 4, 3.18f, 2.38f, 1.30f}, {3, 6, 3.15f, 3.16f, 1.24f},
+    {4, 2, 3.59f, 2.09f, 1.02f}, {4, 4, 3.95f, 3.09f, 1.24f}, {4, 6, 4.16f, 4.00f, 1.32f},
+    {6, 6, 4.70f, 4.42f, 2.05f}, {6, 16, 5.34f, 9.72f, 3.58f}, {8, 6, 5.37f, 5.44f, 2.54f},
+    {8, 16, 6.02f, 11.06f, 4.30f},
+    {2, 6, 3.56f, 4.16f, 2.38f}, {3, 6, 3.61f, 4.36f, 2.33f}, {4, 6, 4.21f, 4.76f, 2.10f}};
+constexpr int kMidShapeCount = sizeof(kMidShapes) / sizeof(kMidShapes[0]);
+constexpr int kMidFirstNT = 13;
+
+float estimate_us(float r, int K, float fix, float round, float fill) {
+  return fix * fmaxf(1.0f, r) + (float)K / 1024.0f * (round * ceilf(r) + fill * fminf(1.0f, r));
+}
+
+// One row group and 96 MB of weights or more: the stream bounds the call, and the six-block
+// shapes with non-temporal loads are the fastest (33.0 us at 64 x 4096 -> 2 x 11008 GLU,
+// 180 MB; the two- and four-block shapes 36 and 40).  Otherwise the shape of the least
+// estimated time, if that is below 0.9 of the tile kernel's: over the shapes of the fit the
+// rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60), no
+// shape runs 5% slower.  More than 1536 rows are outside the fit, and outputs narrower than
+// 256 packed columns keep the tiles' one chain of sums over K (the automatic tile there is
+// bitwise the forced one).
+int mid_shape(int M, int K, int NP, bool glu) {
+  if (M > kMidMaxM || NP < 256) return -1;
+  const int npb = NP / 16;
+  const bool stream = (int64_t)K * NP * 2 >= 96 * 1000 * 1000;
+  int best = -1;
+  float best_us = 0.9f * prefill_estimate_us(M, K, NP, glu);
+  for (int i = 0; i < kMidShapeCount; ++i) {
+    const MidShape& s = kMidShapes[i];
+    const int groups = (M + 16 * s.mb - 1) / (16 * s.mb);
+    const bool nt = i >= kMidFirstNT;
+    if (stream && groups == 1 ? s.blocks != 6 || (!nt && s.mb <= 4) : nt) continue;
+    const int64_t wgs = (int64_t)groups * ((npb + s.blocks - 1) / s.blocks);
+    const float us = estimate_us((float)wgs / 256.0f, K, s.fix, s.round, s.fill);
+    if (us < best_us) {
+      best_us = us;
+      best = i;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_mid_bf16(const PrefillArgs& p, int shape) {
+  switch (p.epi) {
+    case EPI_RMS: return launch_mid_epi<EPI_RMS>(p, shape);
+    case EPI_GLU: return launch_mid_epi<EPI_GLU>(p, shape);
+    case EPI_LN: return launch_mid_epi<EPI_LN>(p, shape);
+    case EPI_NONE: return launch_mid_epi<EPI_NONE>(p, shape);
+    case EPI_GLU_NOSCALE: return launch_mid_epi<EPI_GLU_NOSCALE>(p, shape);
+    case EPI_REGLU: return launch_mid_epi<EPI_REGLU>(p, shape);
+    case EPI_BILINEAR: return launch_mid_epi<EPI_BILINEAR>(p, shape);
+    case EPI_GLU_DEFER: return launch_mid_epi<EPI_GLU_DEFER>(p, shape);
+    case EPI_RELU_DEFER: return launch_mid_epi<EPI_RELU_DEFER>(p, shape);
+    case EPI_ROWSCALE: return launch_mid_epi<EPI_ROWSCALE>(p, shape);
+    case EPI_ROPE: return launch_mid_epi<EPI_ROPE>(p, shape);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace fn

@@ -1,0 +1,9 @@
+// Kinds of the middle-row kernel (mid_kernel.h), split over files that compile in parallel.
+#include "mid_kernel.h"
+
+namespace fn {
+
+template hipError_t launch_mid_epi<EPI_RMS>(const PrefillArgs&, int);
+template hipError_t launch_mid_epi<EPI_GLU>(const PrefillArgs&, int);
+
+}  // namespace fn

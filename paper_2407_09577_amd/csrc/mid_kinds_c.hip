@@ -1,0 +1,10 @@
+// Kinds of the middle-row kernel (mid_kernel.h), split over files that compile in parallel.
+#include "mid_kernel.h"
+
+namespace fn {
+
+template hipError_t launch_mid_epi<EPI_GLU_NOSCALE>(const PrefillArgs&, int);
+template hipError_t launch_mid_epi<EPI_ROPE>(const PrefillArgs&, int);
+template hipError_t launch_mid_epi<EPI_ROWSCALE>(const PrefillArgs&, int);
+
+}  // namespace fn

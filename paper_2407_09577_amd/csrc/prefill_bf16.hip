@@ -879,6 +879,22 @@ static int auto_tile(int M, int NP, bool glu) {
 constexpr int kK64MinK96 = 512;
 constexpr int kK64MinK128 = 2048;
 
+// Time of those tiles, for the choice between them and the middle-row kernel: the form of
+// mid_bf16.hip's estimates (r: tiles per compute unit), fitted to the same measurements within
+// 4 to 11% rms (835 shapes on 128 x 96 tiles, 492 GLU and 78 linear ones on 128 x 128, 18 on
+// 256 x 256).
+float prefill_estimate_us(int M, int K, int NP, bool glu) {
+  const int tile = auto_tile(M, NP, glu);
+  const int bm = tile == TILE_256x256_W8_PF_SP ? 256 : 128;
+  const int bn = tile == TILE_256x256_W8_PF_SP ? 256 : tile == TILE_128x96_W8 ? 96 : 128;
+  const float r = (float)((int64_t)((M + bm - 1) / bm) * ((NP + bn - 1) / bn)) / 256.0f;
+  if (bm == 256) return estimate_us(r, K, 17.1f, 13.8f, 3.3f) + 7.9f * (float)K / 1024.0f * fmaxf(1.0f, r);
+  if (bn == 96) return estimate_us(r, K, 4.56f, 5.21f, 3.07f);
+  if (glu) return estimate_us(r, K, 4.18f, 5.84f, 3.72f) + 0.58f * (float)K / 1024.0f * fmaxf(1.0f, r);
+  if (K >= kK64MinK128) return estimate_us(r, K, 2.45f, 7.79f, 0.53f) + 1.27f * (float)K / 1024.0f * fmaxf(1.0f, r);
+  return estimate_us(r, K, 4.05f, 2.09f, 2.59f) + 5.33f * (float)K / 1024.0f * fmaxf(1.0f, r);
+}
+
 template <int EPI>
 static hipError_t launch_prefill_epi(const PrefillArgs& p) {
   int tile = p.tile;
@@ -961,6 +977,10 @@ static hipError_t launch_prefill_epi(const PrefillArgs& p) {
 }
 
 hipError_t launch_prefill_bf16(const PrefillArgs& p) {
+  if (p.tile == TILE_AUTO && !p.gs && p.epi != EPI_HEADNORM) {
+    const int shape = mid_shape(p.M, p.K, p.NP, epi_is_glu(p.epi));
+    if (shape >= 0) return launch_mid_bf16(p, shape);
+  }
   switch (p.epi) {
     case EPI_RMS: return launch_prefill_epi<EPI_RMS>(p);
     case EPI_GLU: return launch_prefill_epi<EPI_GLU>(p);
