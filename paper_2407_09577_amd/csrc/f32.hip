@@ -1,7 +1,8 @@
-// fp32 fused norm-then-project kernel (small fp32 problems; exact fp32 products,
-// no reduced-precision matrix-core modes).
+// fp32 fused norm-then-project kernels (exact fp32 products, no reduced-precision matrix-core
+// modes): two on the vector units, and one on the fp32 matrix cores for all but the smallest
+// calls.
 //
-// A workgroup owns a BM x 64 output tile (BM = 16 RI rows) and KS groups of 256
+// f32_kernel.  A workgroup owns a BM x 64 output tile (BM = 16 RI rows) and KS groups of 256
 // threads split K between them: group g takes the 64-deep k steps g, g + KS, ...,
 // staging its activation and weight tiles in its own LDS buffers.  The threads
 // that stage an activation row also accumulate its sum of squares (and sum, for
@@ -547,20 +548,210 @@ __global__ __launch_bounds__(256) void f32_few_rows_kernel(const float* __restri
   }
 }
 
+// Matrix-core kernel: fp32 operands, fp32 products and sums (v_mfma_f32_16x16x4_f32, whose
+// operands are not rounded).  A workgroup owns 16 MB rows x 64 packed columns, and its KS waves
+// split K: wave w takes the 16-deep k blocks w, w + KS, ... and holds the whole tile's partial
+// products, so nothing is staged or read twice inside a workgroup and the K loop has no barrier.
+//
+// Operands.  Lane l = 16 q + r loads the activations of row r, k = 4 q .. 4 q + 3 of the block
+// (one float4 per 16 rows: 64 contiguous bytes of each row) and, for e = 0..3, the weights of
+// k = 4 q + e, columns 4 r .. 4 r + 3 (256 contiguous bytes of each k).  Matrix-core op (t, e, j)
+// multiplies element e of row block t with component j of weight e: its four k are 4 q + e and
+// its sixteen columns 4 r + j, an order of K and of the columns that both operands share.  The
+// lane ends with row r and, over j, four consecutive columns 16 q + 4 i .. 4 i + 3 for every
+// accumulator component i.  Loads run one block ahead in registers, 16 MB matrix-core ops of 32
+// cycles before their use.
+//
+// Bound by the fp32 matrix rate (154 TFLOP/s measured with a large product) where the tiles
+// fill the chip.  500 x 2048 -> 2048: 163 us on the vector units (f32_kernel, whose operands
+// come from LDS one value per multiply-add), 41 us here.
+template <int EPI, bool GS, int MB, int KS>
+__global__ __launch_bounds__(64 * KS, 1) void f32_mfma_kernel(const float* __restrict__ a, int M, int K, int lda,
+                                                              const float* __restrict__ ws, int NP, int KP,
+                                                              int ncols, float* __restrict__ y, int ldy, EpiArgs ep) {
+  using ST = StatT<EPI>;
+  constexpr bool kLN = EPI == EPI_LN, kSS = epi_needs_ss(EPI);
+  constexpr int BM = 16 * MB, LDT = 68;  // rows; floats per staged row (16 rows of one column: 16 bank groups)
+  __shared__ __attribute__((aligned(16))) float part[KS][BM][LDT];
+  __shared__ ST row_ss[KS][BM], row_sa[KS][BM];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tm, tn;
+  tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, gridDim.y, gridDim.x, tm, tn);
+  const int m0 = tm * BM, p0 = tn * 64;
+  const int r = lane & 15, q = lane >> 4;
+  const int rows = min(BM, M - m0);
+  const __amdgpu_buffer_rsrc_t ars =
+      make_rsrc(a + (int64_t)m0 * lda, (uint32_t)(((int64_t)(rows - 1) * lda + K) * 4));
+  const __amdgpu_buffer_rsrc_t wrs = make_rsrc(ws, (uint32_t)((int64_t)KP * NP * 4));
+  const __amdgpu_buffer_rsrc_t grs = make_rsrc(GS ? ep.g_rt : nullptr, GS ? (uint32_t)K * 4 : 0u);
+  const bool col_ok = p0 + 4 * r < NP;  // NP is a multiple of 16: a quad is wholly inside or outside
+  const unsigned woff = (unsigned)(p0 + 4 * r) * 4u, wrow = (unsigned)NP * 4u;
+
+  float piv[MB];
+#pragma unroll
+  for (int t = 0; t < MB; ++t) piv[t] = kLN && m0 + 16 * t + r < M ? a[(int64_t)(m0 + 16 * t + r) * lda] : 0.0f;
+
+  // Offsets past an operand are selected to one that reads zeros (through an empty asm, so that
+  // the compiler keeps one load of a selected offset).  K is a multiple of 4.
+  auto opaque = [](unsigned v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto load = [&](int kb, f32x4 (&A)[MB], f32x4 (&W)[4], f32x4& G) __attribute__((always_inline)) {
+    const int k = kb * 16 + 4 * q;
+    const bool live = k < K;
+#pragma unroll
+    for (int t = 0; t < MB; ++t)
+      A[t] = __builtin_bit_cast(
+          f32x4, load_buf16(ars, opaque(live ? (unsigned)((16 * t + r) * lda + k) * 4u : kOobOffset)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      W[e] = __builtin_bit_cast(
+          f32x4, load_buf16(wrs, opaque(live && col_ok ? (unsigned)(k + e) * wrow + woff : kOobOffset)));
+    if constexpr (GS) G = __builtin_bit_cast(f32x4, load_buf16(grs, opaque(live ? (unsigned)k * 4u : kOobOffset)));
+  };
+
+  constexpr int ES = 4 / MB;  // chains of sums per output, over e % ES: K / (4 KS ES) ops long
+  f32x4 acc[ES][MB][4];
+  ST ss[MB], sa[MB];
+#pragma unroll
+  for (int t = 0; t < MB; ++t) {
+    ss[t] = sa[t] = ST(0);
+#pragma unroll
+    for (int s = 0; s < ES; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[s][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto compute = [&](int kb, f32x4 (&A)[MB], const f32x4 (&W)[4], const f32x4& G) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < MB; ++t) {
+      f32x4 av = A[t];
+      if constexpr (kLN) {  // shifted by the row's pivot; a quad past K stays zero
+        const float p = kb * 16 + 4 * q < K ? piv[t] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[e] -= p;
+        const double x = av[0], yv = av[1], z = av[2], w = av[3];
+        ss[t] += (x * x + yv * yv) + (z * z + w * w);
+        sa[t] += (x + yv) + (z + w);
+      } else if constexpr (kSS) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss[t] = fmaf(av[e], av[e], ss[t]);
+      }
+      if constexpr (GS) {  // run-time g (unfolded W): a_k g_k in fp32
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[e] *= G[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[e % ES][t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[e][j], av[e], acc[e % ES][t][j], 0, 0, 0);
+    }
+  };
+
+  const int KB = (K + 15) / 16;
+  f32x4 A0[MB], A1[MB], W0[4], W1[4], G0, G1;
+  load(wave, A0, W0, G0);
+  for (int kb = wave; kb < KB; kb += 2 * KS) {
+    load(kb + KS, A1, W1, G1);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(kb, A0, W0, G0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(kb + 2 * KS, A0, W0, G0);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(kb + KS, A1, W1, G1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // Partials to LDS, added over the waves in order (deterministic) by the threads that finish
+  // them: thread (tx, ty) of 256-thread group g takes rows ty + 16 i of the group's share and
+  // columns tx + 16 j, as the other fp32 kernels' epilogue.
+#pragma unroll
+  for (int t = 0; t < MB; ++t) {
+    if constexpr (kSS) {
+      ss[t] += __shfl_xor(ss[t], 16);
+      ss[t] += __shfl_xor(ss[t], 32);
+      if constexpr (kLN) {
+        sa[t] += __shfl_xor(sa[t], 16);
+        sa[t] += __shfl_xor(sa[t], 32);
+      }
+    }
+    if (lane < 16) {
+      row_ss[wave][16 * t + r] = ss[t];
+      row_sa[wave][16 * t + r] = sa[t];
+    }
+#pragma unroll
+    for (int s = 1; s < ES; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[0][t][j] += acc[s][t][j];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4*>(&part[wave][16 * t + r][16 * q + 4 * i]) =
+          f32x4{acc[0][t][0][i], acc[0][t][1][i], acc[0][t][2][i], acc[0][t][3][i]};
+  }
+  __syncthreads();
+  constexpr int EG = MB < KS / 4 ? MB : KS / 4, RI = MB / EG;  // finishing groups, row blocks of each
+  const int grp = threadIdx.x >> 8, tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) & 15;
+  if (grp >= EG) return;
+  float out[RI][4];
+  ST rss[RI], rsa[RI];
+#pragma unroll
+  for (int i = 0; i < RI; ++i) {
+    const int row = 16 * (grp * RI + i) + ty;
+    rss[i] = rsa[i] = ST(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[i][j] = part[0][row][tx + 16 * j];
+#pragma unroll
+    for (int w = 0; w < KS; ++w) {
+      rss[i] += row_ss[w][row];
+      rsa[i] += row_sa[w][row];
+      if (w > 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[i][j] += part[w][row][tx + 16 * j];
+      }
+    }
+  }
+  f32_epilogue<EPI, RI, 4>(out, rss, rsa, tx, ty, m0 + 16 * grp * RI, p0, M, ncols, y, ldy, ep, tn == 0);
+}
+
 // Tile configurations (kF32CfgCount): 0 automatic, 1 = 64-row tiles with one k group,
-// 2 = 16-row tiles of 64 columns with four k groups, 3 = the few-row kernel.  Automatic:
-// the 64-row tiles when they make at least 128 workgroups, else the 16 x 64 tiles when
-// they make at least 256 (their LDS staging reads each operand once per tile), else the
-// few-row kernel (its narrow tiles spread few rows over many workgroups; its operands go
-// through the vector memory path four times, which costs more than it gains once the
-// 16 x 64 tiles fill the chip).
+// 2 = 16-row tiles of 64 columns with four k groups, 3 = the few-row kernel.
+//
+// Automatic (2222 random shapes of 1..2048 rows, K 64..4096, 8..8192 columns, linear and GLU,
+// on MI355X): the few-row kernel when 16 x 64 tiles would be 32 or fewer (its narrow tiles
+// spread them over more units: 16 x 576 -> 576 6.1 us, 7.0 on the matrix cores), and for one or
+// two rows of up to 64 tiles (1 x 332 -> 4084: 5.5 and 6.6).  Otherwise the matrix-core kernel:
+// 32-row tiles with four waves from 384 tiles on (1024 x 2048 -> 4096: 146 us, 170 with 16
+// rows), else 16-row tiles, with four waves from 128 tiles and eight below (64 x 2048 -> 2048:
+// 14.3 us, 14.9 with four).  The choice takes 0.51 of the time of the vector kernels it
+// replaces (geometric mean; 500 x 2048 -> 2048: 165 -> 41 us, 16 x 2048 -> 8192: 162 -> 15), no
+// shape is 8% slower, and the error against fp64 is at most theirs: a chain of sums is
+// K / 64 (32 rows: K / 32) ops long and shorter with eight waves.
+
+template <int EPI, bool GS, int MB, int KS>
+static void launch_f32_mfma(const F32Args& p) {
+  dim3 grid((p.NP + 63) / 64, (p.M + 16 * MB - 1) / (16 * MB));
+  hipLaunchKernelGGL((f32_mfma_kernel<EPI, GS, MB, KS>), grid, dim3(64 * KS), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
+                     p.NP, p.KP, p.ncols, p.y, p.ldy, p.ep);
+}
 
 template <int EPI, bool GS = false>
 static hipError_t launch_f32_epi(const F32Args& p) {
   int cfg = p.cfg;
   if (cfg == 0) {
-    const int64_t nt = (p.NP + 63) / 64;
-    cfg = (int64_t)((p.M + 63) / 64) * nt >= 128 ? 1 : (int64_t)((p.M + 15) / 16) * nt >= 256 ? 2 : 3;
+    const int64_t nt = (p.NP + 63) / 64, tiles = nt * ((p.M + 15) / 16);
+    if (tiles <= 32 || (p.M <= 2 && nt <= 64)) {
+      cfg = 3;
+    } else if (p.M > 65535 * 16) {  // more 16-row tiles than a grid dimension holds
+      cfg = 1;
+    } else {
+      if (nt * ((p.M + 31) / 32) >= 384) launch_f32_mfma<EPI, GS, 2, 4>(p);
+      else if (tiles >= 128) launch_f32_mfma<EPI, GS, 1, 4>(p);
+      else launch_f32_mfma<EPI, GS, 1, 8>(p);
+      return hipGetLastError();
+    }
   }
   if (cfg == 1) {
     dim3 grid((p.NP + 63) / 64, (p.M + 63) / 64);
