@@ -9,6 +9,7 @@ this module raises on first use -- there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -102,20 +103,25 @@ def _torch_dtype(code: int) -> torch.dtype:
     return torch.bfloat16 if code == FN_BF16 else torch.float32
 
 
+# The calls below run once per fused op, beside kernels of a few microseconds, so they keep to
+# plain integers (which ctypes converts by the declared argument types) and to one query per
+# property: 16 x 576 -> 576 took 11.8 us a call with pointer and stream objects and a size
+# query through the library, 8.0 us now (3.6 of them the launch).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2 or t.stride(1) != 1:
+    s = t.stride()
+    if len(s) != 2 or s[1] != 1:
         raise ValueError("expected a row-major 2-D tensor (unit column stride)")
-    return t.stride(0)
+    return s[0]
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    if stream is None:  # the current stream of the current device
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _vec(t, n, name):
@@ -132,12 +138,16 @@ def _new_out(M: int, N: int, like: torch.Tensor) -> torch.Tensor:
     any N works; the result is then a view of the first N columns."""
     per = 16 // like.element_size()
     ld = (N + per - 1) // per * per
-    buf = torch.empty(M, ld, dtype=like.dtype, device=like.device)
+    buf = like.new_empty(M, ld)
     return buf if ld == N else buf[:, :N]
 
 
 def fold_weights_size(K: int, N: int, layout: int = FN_LAYOUT_LINEAR, ws_dtype: int = FN_BF16) -> int:
     return _load().fold_weights_size(K, N, layout, ws_dtype)
+
+
+# A pure function of four integers, asked again by every call on the same weight shape.
+_packed_bytes = functools.lru_cache(maxsize=4096)(fold_weights_size)
 
 
 # The C ABI takes raw device pointers and sizes the kernels' reads from the shape
@@ -149,7 +159,7 @@ def _guard(where, tensors=(), packed=None, outs=(), nbytes=()):
     nbytes = ((tensor, bytes needed, name), ...).  Size checks come first, then devices."""
     if packed is not None:
         Wst, K, N, layout, code = packed
-        need = fold_weights_size(K, N, layout, code)
+        need = _packed_bytes(K, N, layout, code)
         # need == 0: invalid geometry, which the library itself rejects with its status
         if need and Wst.numel() * Wst.element_size() < need:
             raise ValueError(f"{where}: the packed weight holds {Wst.numel() * Wst.element_size()} bytes; "
@@ -168,10 +178,11 @@ def _guard(where, tensors=(), packed=None, outs=(), nbytes=()):
             continue
         if not t.is_cuda:
             raise ValueError(f"{where}: every tensor must be a GPU tensor (got one on {t.device})")
+        d = t.get_device()
         if dev is None:
-            dev = t.device
-        elif t.device != dev:
-            raise ValueError(f"{where}: tensors on {dev} and {t.device}; all must be on one GPU")
+            dev = d
+        elif d != dev:
+            raise ValueError(f"{where}: tensors on cuda:{dev} and {t.device}; all must be on one GPU")
 
 
 def fold_weights(W: torch.Tensor, g, beta=None, layout: int = FN_LAYOUT_LINEAR, ws_dtype=None,
