@@ -22,8 +22,10 @@ extern template hipError_t launch_mid_epi<EPI_ROPE>(const PrefillArgs&, int);
 // A workgroup's time per k is constant, a round ends when its last workgroup does, and units
 // that share the memory slow each other down a little.  The constants are least-squares fits
 // over 1423 random bf16 shapes (17..1500 rows, K 512..8192, 512..20480 columns, linear and
-// GLU), each shape of the table within 5 to 18% rms.  Shapes 13..15 are 2, 5 and 8 with
-// non-temporal weight loads.
+// GLU; shapes 16 and 17 over 1458 of 65..1536 rows), each shape of the table within 5 to 18%
+// rms.  Shapes 13..15 are 2, 5 and 8 with non-temporal weight loads; shape 17's three column
+// blocks per wave hold no whole gate/up pairs.  The last two took 2% off the mean over their sample
+// (333 x 4096 -> 12288: 53.2 -> 48.3 us).
 struct MidShape {
   int mb, blocks;
   float fix, round, fill;
@@ -34,9 +36,10 @@ static constexpr MidShape kMidShapes[] = {
     {4, 2, 3.59f, 2.09f, 1.02f}, {4, 4, 3.95f, 3.09f, 1.24f}, {4, 6, 4.16f, 4.00f, 1.32f},
     {6, 6, 4.70f, 4.42f, 2.05f}, {6, 16, 5.34f, 9.72f, 3.58f}, {8, 6, 5.37f, 5.44f, 2.54f},
     {8, 16, 6.02f, 11.06f, 4.30f},
-    {2, 6, 3.56f, 4.16f, 2.38f}, {3, 6, 3.61f, 4.36f, 2.33f}, {4, 6, 4.21f, 4.76f, 2.10f}};
+    {2, 6, 3.56f, 4.16f, 2.38f}, {3, 6, 3.61f, 4.36f, 2.33f}, {4, 6, 4.21f, 4.76f, 2.10f},
+    {4, 8, 3.81f, 4.45f, 1.56f}, {7, 12, 5.78f, 8.33f, 2.72f}};
 constexpr int kMidShapeCount = sizeof(kMidShapes) / sizeof(kMidShapes[0]);
-constexpr int kMidFirstNT = 13;
+constexpr int kMidFirstNT = 13, kMidLastNT = 15, kMidLinearOnly = 17;
 
 float estimate_us(float r, int K, float fix, float round, float fill) {
   return fix * fmaxf(1.0f, r) + (float)K / 1024.0f * (round * ceilf(r) + fill * fminf(1.0f, r));
@@ -59,7 +62,8 @@ int mid_shape(int M, int K, int NP, bool glu) {
   for (int i = 0; i < kMidShapeCount; ++i) {
     const MidShape& s = kMidShapes[i];
     const int groups = (M + 16 * s.mb - 1) / (16 * s.mb);
-    const bool nt = i >= kMidFirstNT;
+    const bool nt = i >= kMidFirstNT && i <= kMidLastNT;
+    if (glu && i == kMidLinearOnly) continue;
     if (stream && groups == 1 ? s.blocks != 6 || (!nt && s.mb <= 4) : nt) continue;
     const int64_t wgs = (int64_t)groups * ((npb + s.blocks - 1) / s.blocks);
     const float us = estimate_us((float)wgs / 256.0f, K, s.fix, s.round, s.fill);

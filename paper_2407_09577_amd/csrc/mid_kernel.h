@@ -23,7 +23,7 @@
 //
 // Measured on MI355X against the 128-row tiles (graph replay): 64 x 4096 -> 2 x 11008 GLU
 // 43.3 -> 33.0 us, 64 x 4096 -> 4096 24.8 -> 10.5, 32 x 8192 -> 1024 44.2 -> 14.7, 333 x 4096
-// -> 12288 62.4 -> 51.5, 1024 x 5120 -> 576 33.5 -> 19.3.  Slower and not kept: register rings
+// -> 12288 62.4 -> 48.3, 1024 x 5120 -> 576 33.5 -> 19.3.  Slower and not kept: register rings
 // of three and four sets (35.1 -> 37..39 us at 64 rows GLU) and a step sequence over a
 // three-slot LDS ring with the barrier inside it (37.1).
 #pragma once
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(64 * CW * KS, 1) void mid_bf16_kernel(
 
 template <int MB, int NCB, int CW, int KS, int EPI, int CPOL = 0>
 static hipError_t launch_mid_cfg(const PrefillArgs& p) {
-  constexpr int U = NCB * CW == 4 ? 2 : 1;
+  constexpr int U = NCB * CW == 4 || NCB * CW == 8 ? 2 : 1;
   const int groups = (p.M + 16 * MB - 1) / (16 * MB);
   const int col_tiles = (p.NP / 16 + NCB * CW - 1) / (NCB * CW);
   hipLaunchKernelGGL((mid_bf16_kernel<MB, NCB, CW, KS, U, EPI, CPOL>), dim3(col_tiles * groups),
@@ -297,6 +297,9 @@ hipError_t launch_mid_epi(const PrefillArgs& p, int shape) {
     case 13: return launch_mid_cfg<2, 2, 3, 4, EPI, kCachePolicyNT>(p);
     case 14: return launch_mid_cfg<3, 2, 3, 4, EPI, kCachePolicyNT>(p);
     case 15: return launch_mid_cfg<4, 2, 3, 4, EPI, kCachePolicyNT>(p);
+    case 16: return launch_mid_cfg<4, 2, 4, 2, EPI>(p);
+    case 17:
+      if constexpr (!epi_is_glu(EPI)) return launch_mid_cfg<7, 3, 4, 2, EPI>(p);
   }
   return hipErrorInvalidValue;
 }
