@@ -340,6 +340,12 @@ static hipError_t launch_decode_cfg(const DecodeArgs& p) {
 //   544 <= npb < 1088    4 blocks x 4 waves x 1
 //   272 <= npb < 544     2 blocks x 4 waves x 2
 //   npb < 272            2 blocks x 8 waves x 1
+//   npb <= 256, no GLU   1 block x 8 waves x 2, loads cached: a compute unit has room for every
+//                        workgroup, and one block each puts twice as many to work, each with as
+//                        many bytes in flight (measured over 456 random shapes of 1..16 rows, K
+//                        512..8192: 15 to 24% less time than 2 x 8 x 1 at any width up to 256,
+//                        weights cached or not, the worst shape 4% more; 16 x 4096 -> 4096 11.0
+//                        -> 8.4 us, 4 x 6144 -> 689 10.9 -> 6.9; at 257..400 blocks it loses 8%)
 // With run-time g the wide case takes 8 x 2 x 2 (M <= 8) or 2 x 1 x 4 (the g
 // loads want four blocks per set).
 template <int EPI, bool GS>
@@ -353,6 +359,8 @@ static hipError_t launch_decode_auto(const DecodeArgs& p) {
       return launch_decode_cfg<2, 1, 4, EPI, true, kCachePolicyNT, false, 4>(p);
     }
   }
+  if constexpr (!GS && !epi_is_glu(EPI))
+    if (npb <= 256) return launch_decode_cfg<1, 8, 2, EPI, true>(p);
   if (npb >= 544) return launch_decode_cfg<4, 4, 1, EPI, true, kCachePolicyNT, GS>(p);
   if (npb >= 272) return launch_decode_cfg<2, 4, 2, EPI, true, kCachePolicyNT, GS>(p);
   return launch_decode_cfg<2, 8, 1, EPI, true, kCachePolicyNT, GS>(p);
