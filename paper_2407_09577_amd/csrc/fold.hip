@@ -103,8 +103,9 @@ __device__ __forceinline__ void load_v8(const float* __restrict__ v, int64_t k0,
   for (int e = 0; e < 8; ++e) x[e] = v && k0 + e < K ? v[k0 + e] : none;
 }
 
-// The stored bf16 values of eight k of a column, as 16 bytes.
-__device__ __forceinline__ u32x4 fold8_bf16(const float (&g)[8], const float (&w)[8]) {
+// The stored bf16 values of eight k of a column, as 16 bytes; +0 without a column, whatever g
+// (k past K have w = +0 and g = 1).
+__device__ __forceinline__ u32x4 fold8_bf16(const float (&g)[8], const float (&w)[8], bool column) {
   bool special = false;
   u32x4 r;
 #pragma unroll
@@ -118,6 +119,8 @@ __device__ __forceinline__ u32x4 fold8_bf16(const float (&g)[8], const float (&w
       r[i] = dbl_to_bf16_rne((double)g[2 * i] * (double)w[2 * i]) |
              ((unsigned)dbl_to_bf16_rne((double)g[2 * i + 1] * (double)w[2 * i + 1]) << 16);
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = column ? r[i] : 0u;
   return r;
 }
 
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(256) void fold_pack_bf16_kernel(const T* __restrict
     if (kb >= KB) break;
     float g[8];
     load_v8(in.g, (int64_t)kb * kKB + (lane >> 4) * 8, in.K, in.gvec, 1.0f, g);
-    out[((int64_t)kb * NPB + cb) * 64 + lane] = fold8_bf16(g, w[i]);
+    out[((int64_t)kb * NPB + cb) * 64 + lane] = fold8_bf16(g, w[i], n >= 0);
   }
 }
 
@@ -183,7 +186,7 @@ __global__ __launch_bounds__(1024) void fold_sums_kernel(const T* __restrict__ W
     load_k8(W, in.sk, in.sn, k0, n, in.K, in.vec, w);
     load_v8(in.g, k0, in.K, in.gvec, 1.0f, g);
     if constexpr (PACK) {
-      const u32x4 h = fold8_bf16(g, w);
+      const u32x4 h = fold8_bf16(g, w, n >= 0);
       out[((int64_t)kb * NPB + cb) * 64 + lane] = h;
 #pragma unroll
       for (int i = 0; i < 4; ++i) cs += (double)bf16_lo(h[i]) + (double)bf16_hi(h[i]);
@@ -232,14 +235,15 @@ __global__ __launch_bounds__(256) void fold_pack_f32_kernel(const T* __restrict_
   if (in.sk == 1) {
     const int64_t k = k0 + (t & 31), kc = k < in.K ? k : 0;
     const float g = in.g ? in.g[kc] : 1.0f;
+    bool live[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int64_t pl = p0 + (t >> 5) + 8 * i, n = pl < NP ? logical_col(pl, in.N, in.glu) : -1;
-      const float w = widen(W[kc + (n >= 0 ? n : 0) * in.sn]);
-      v[i] = n >= 0 && k < in.K ? w : 0.0f;
+      v[i] = widen(W[kc + (n >= 0 ? n : 0) * in.sn]);
+      live[i] = n >= 0 && k < in.K;
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) tile[t & 31][(t >> 5) + 8 * i] = fold_f32(g, v[i]);
+    for (int i = 0; i < 8; ++i) tile[t & 31][(t >> 5) + 8 * i] = live[i] ? fold_f32(g, v[i]) : 0.0f;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = tile[(t >> 6) + 4 * i][t & 63];
@@ -248,13 +252,12 @@ __global__ __launch_bounds__(256) void fold_pack_f32_kernel(const T* __restrict_
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int64_t k = k0 + (t >> 6) + 4 * i, kc = k < in.K ? k : 0;
-      const float w = widen(W[kc * in.sk + (n >= 0 ? n : 0) * in.sn]);
-      v[i] = n >= 0 && k < in.K ? w : 0.0f;
+      v[i] = widen(W[kc * in.sk + (n >= 0 ? n : 0) * in.sn]);
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int64_t k = k0 + (t >> 6) + 4 * i;
-      v[i] = fold_f32(in.g ? in.g[k < in.K ? k : 0] : 1.0f, v[i]);
+      v[i] = n >= 0 && k < in.K ? fold_f32(in.g ? in.g[k] : 1.0f, v[i]) : 0.0f;
     }
   }
   if (p >= NP) return;

@@ -89,3 +89,23 @@ def test_sums_follow_the_stored_values(src, ws, K, N):
         if ref is not None:
             assert all(torch.equal(a, b) for a, b in zip(ref, (Ws, cs, cb))), name
         ref = (Ws, cs, cb)
+
+
+@pytest.mark.parametrize("ws", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("K,N,sums", [(72, 33, False), (520, 70, False), (200, 5, True)])
+def test_padding_is_positive_zero(ws, K, N, sums):
+    """Rows past K and columns past N are +0 in every byte, whatever g holds (negative, infinite, NaN)."""
+    from paper_2407_09577_amd import flashnorm as fn
+    W, g = _values(K, N, ws, K)
+    g[0], g[1], g[2::2] = float("nan"), float("-inf"), -1.0
+    for name, view in _views(W):
+        Ws, _, _ = fn.fold_weights(view, g.cuda(), colsum=sums, ws_dtype=ws)
+        KP = (K + 63) // 64 * 64
+        if ws == torch.bfloat16:  # [k block][column block][k chunk][column][8 k]
+            bits = Ws.flatten().view(torch.int16)
+            bits = bits.view(KP // 32, -1, 4, 16, 8).permute(0, 2, 4, 1, 3).reshape(KP, -1)
+        else:
+            bits = Ws.flatten().view(torch.int32).view(KP, -1)
+        assert bits.shape[1] >= N
+        assert not bits[K:].any() and not bits[:, N:].any(), name
+        assert bits[:K, :N].any(), name
