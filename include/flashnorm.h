@@ -65,9 +65,12 @@ typedef enum { FN_F32 = 0, FN_BF16 = 1 } fn_dtype;
 typedef enum { FN_LAYOUT_LINEAR = 0, FN_LAYOUT_GLU = 1 } fn_layout;
 
 /* Kernel selection (Sec. 6 and App. "Production path": shape-specialised dispatch).
- * AUTO picks by M; PREFILL forces the matrix-core tile kernel (any M);
- * DECODE forces the bandwidth-bound few-row kernel (bf16, M <= 16, else
- * FN_ERR_UNSUPPORTED).  fp32 always runs the fp32 kernel. */
+ * AUTO picks by the shape (bf16: the few-row kernel up to 16 rows, then the
+ * middle-row kernel or the tile kernel, whichever is expected to be faster);
+ * PREFILL forces the matrix-core tile kernel (any M); DECODE forces the
+ * bandwidth-bound few-row kernel (bf16, M <= 16, else FN_ERR_UNSUPPORTED).
+ * fp32 always runs the fp32 kernels: the few-row kernel or the fp32 matrix-core
+ * kernel, chosen by the shape, unless a configuration is named (below). */
 typedef enum { FN_PATH_AUTO = 0, FN_PATH_PREFILL = 1, FN_PATH_DECODE = 2 } fn_path;
 
 /* Tuning override: bits 8..15 of a path argument may name one of the library's
@@ -76,7 +79,8 @@ typedef enum { FN_PATH_AUTO = 0, FN_PATH_PREFILL = 1, FN_PATH_DECODE = 2 } fn_pa
  * 2 = 16-row tiles with K split over four thread groups, 3 = the few-row kernel:
  * 16-row tiles of 4, 8 or 16 columns (8 or 16 for a GLU, 64 with per-head norms,
  * the width chosen by the workgroup count) with K split over 256 / width thread
- * groups; 0 = automatic choice);
+ * groups; 0 = automatic choice; the middle-row kernel and the fp32 matrix-core
+ * kernel are reached by the automatic choice alone);
  * values it does not know return FN_ERR_VALUE.  Results are identical for every configuration up to
  * floating-point summation order. */
 #define FN_PATH_TILE_SHIFT 8

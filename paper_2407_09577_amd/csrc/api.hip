@@ -152,6 +152,11 @@ int run_op(const OpDesc& d) {
   fn::PrefillArgs p{(const __bf16*)d.a, (int)d.M, (int)d.K, (int)d.lda, (const __bf16*)d.ws, NP, KP,
                     (int)d.ncols, (__bf16*)d.y, (int)d.ldy, d.epi, d.path >> FN_PATH_TILE_SHIFT, d.ep,
                     d.stream, d.gs};
+  // The middle-row kernel is an automatic choice alone: PREFILL and a named tile force the tile kernel.
+  if (d.path == FN_PATH_AUTO && !d.gs && d.epi != fn::EPI_HEADNORM) {
+    const int shape = fn::mid_shape(p.M, p.K, p.NP, d.glu);
+    if (shape >= 0) return status_of(fn::launch_mid_bf16(p, shape));
+  }
   return status_of(fn::launch_prefill_bf16(p));
 }
 

@@ -64,8 +64,8 @@ struct PrefillArgs {
 };
 hipError_t launch_prefill_bf16(const PrefillArgs& p);
 
-// Middle rows (mid_bf16.hip): the workgroup shape for a call without a forced tile, or -1 when
-// the many-row tiles are to take it.  Every kind but the per-head norms, no run-time g.
+// Middle rows (mid_bf16.hip): the workgroup shape for a call that leaves the kernel to the library
+// (FN_PATH_AUTO, no named tile), or -1 when the many-row tiles are to take it.  Every kind but the per-head norms, no run-time g.
 constexpr int kMidMaxM = 1536;
 int mid_shape(int M, int K, int NP, bool glu);
 hipError_t launch_mid_bf16(const PrefillArgs& p, int shape);

@@ -977,10 +977,6 @@ static hipError_t launch_prefill_epi(const PrefillArgs& p) {
 }
 
 hipError_t launch_prefill_bf16(const PrefillArgs& p) {
-  if (p.tile == TILE_AUTO && !p.gs && p.epi != EPI_HEADNORM) {
-    const int shape = mid_shape(p.M, p.K, p.NP, epi_is_glu(p.epi));
-    if (shape >= 0) return launch_mid_bf16(p, shape);
-  }
   switch (p.epi) {
     case EPI_RMS: return launch_prefill_epi<EPI_RMS>(p);
     case EPI_GLU: return launch_prefill_epi<EPI_GLU>(p);

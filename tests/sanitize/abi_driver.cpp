@@ -59,6 +59,29 @@ int main() {
   CHECK(lin(16, 200, 200, FN_F32, A, Y, 64, 1e-6f, 2 << FN_PATH_TILE_SHIFT) == FN_OK);
   CHECK(fnstub_last.kind == 3 && fnstub_last.cfg == 2);
 
+  // The middle-row kernel (the stub's chooser offers it for 17 rows and 256 packed columns on) is an
+  // automatic choice alone: PREFILL and a named tile run the tile kernel at any M, as do run-time g and the
+  // per-head norms.
+  auto wide = [](int64_t M, int path) {
+    return flashnorm_linear_ex(P(A), M, 200, 208, FN_BF16, P(W), 256, 1e-6f, nullptr, P(Y), 256, FN_BF16, nullptr, path,
+                               nullptr);
+  };
+  CHECK(wide(333, FN_PATH_AUTO) == FN_OK && fnstub_last.kind == 10 && fnstub_last.NP == 256);
+  CHECK(wide(333, FN_PATH_PREFILL) == FN_OK && fnstub_last.kind == 1);
+  CHECK(wide(1, FN_PATH_PREFILL) == FN_OK && fnstub_last.kind == 1);
+  CHECK(wide(333, 4 << FN_PATH_TILE_SHIFT) == FN_OK && fnstub_last.kind == 1 && fnstub_last.cfg == 4);
+  CHECK(wide(16, FN_PATH_AUTO) == FN_OK && fnstub_last.kind == 2);
+  auto relu = [](int64_t M, int path) {  // a kind that takes no named tile
+    return flashnorm_linear_relu(P(A), M, 200, 208, FN_BF16, P(W), 256, 1e-6f, P(Y), 256, FN_BF16, PF(X), path, nullptr);
+  };
+  CHECK(relu(333, FN_PATH_AUTO) == FN_OK && fnstub_last.kind == 10);
+  CHECK(relu(333, FN_PATH_PREFILL) == FN_OK && fnstub_last.kind == 1);
+  CHECK(flashnorm_linear_unfolded(P(A), 333, 200, 208, FN_BF16, PF(B), P(W), 256, 1e-6f, nullptr, P(Y), 256, FN_BF16,
+                                  nullptr, FN_PATH_AUTO, nullptr) == FN_OK && fnstub_last.kind == 1);
+  CHECK(flashnorm_qkv_headnorm(P(A), 333, 200, 208, FN_BF16, P(W), 8, 4, 16, 1e-6f, PF(X), PF(X), nullptr, 1e-6f,
+                               nullptr, nullptr, nullptr, 0, 1.0f, P(Y), 256, FN_BF16, nullptr, FN_PATH_AUTO,
+                               nullptr) == FN_OK && fnstub_last.kind == 1);
+
   // GLU: F columns out, 2F packed with gate/up pairs.
   CHECK(flashnorm_glu(P(A), 40, 128, 128, FN_BF16, P(W), 45, 1e-6f, P(Y), 48, FN_BF16, nullptr) == FN_OK);
   CHECK(fnstub_last.kind == 1 && fnstub_last.NP == 2 * 48 && fnstub_last.ncols == 45);

@@ -7,7 +7,7 @@
 extern "C" {
 #endif
 typedef struct {
-  int kind;  /* 1 prefill, 2 decode, 3 fp32, 4 fold, 5 unpack, 6 norm rows, 7 head norm, 8 rope, 9 mla */
+  int kind;  /* 1 prefill, 2 decode, 3 fp32, 4 fold, 5 unpack, 6 norm rows, 7 head norm, 8 rope, 9 mla, 10 middle rows */
   int64_t M, K, lda, NP, KP, ncols, ldy, cfg, epi, sk, sn;
 } fnstub_record;
 extern fnstub_record fnstub_last;

@@ -19,6 +19,10 @@ namespace fn {
 hipError_t launch_prefill_bf16(const PrefillArgs& p) {
   return rec(1, p.M, p.K, p.lda, p.NP, p.KP, p.ncols, p.ldy, p.tile, p.epi);
 }
+int mid_shape(int M, int, int NP, bool) { return M > 16 && M <= kMidMaxM && NP >= 256 ? 0 : -1; }
+hipError_t launch_mid_bf16(const PrefillArgs& p, int) {
+  return rec(10, p.M, p.K, p.lda, p.NP, p.KP, p.ncols, p.ldy, p.tile, p.epi);
+}
 hipError_t launch_decode_bf16(const DecodeArgs& p) {
   return rec(2, p.M, p.K, p.lda, p.NP, p.KP, p.ncols, p.ldy, p.cfg, p.epi);
 }

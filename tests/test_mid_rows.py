@@ -93,3 +93,20 @@ def test_rope_matches_projection_then_rotation(M, K, Hq, Hkv, h):
     r[:, : Hq * h] *= 0.5
     want = torch.cat((r, t[:, (Hq + Hkv) * h:]), 1)
     assert float(((y - want).abs().amax(1) / want.abs().amax(1)).max()) <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [3, 40, 333])
+def test_prefill_names_the_tile_kernel(M):
+    # PREFILL forces the tile kernel at any M: the bits of its automatic tile here, 128 x 96.
+    from paper_2407_09577_amd import flashnorm as fn
+    K, N = 512, 3000
+    w = workloads.make("linear", M, K, N, eps=1e-5, seed=M)
+    Ws, _, _ = fn.fold_weights(w.W.cuda(), w.g.cuda())
+    a, s = w.a.cuda(), torch.empty(M, device="cuda")
+    y = fn.flashnorm_linear(a, Ws, N, w.eps, path=fn.FN_PATH_PREFILL)
+    assert torch.equal(y, fn.flashnorm_linear(a, Ws, N, w.eps, path=fn.FN_PATH_PREFILL | (4 << 8)))
+    # A kind that takes no named tile: the same products, unscaled (its sums in the tiles' one order over K).
+    ones = torch.ones(M, device="cuda")
+    z = fn.flashnorm_linear_relu(a, Ws, N, w.eps, s, path=fn.FN_PATH_PREFILL)
+    assert torch.equal(z, fn.rowscale_linear(a, Ws, N, ones, path=fn.FN_PATH_PREFILL).clamp(min=0))
