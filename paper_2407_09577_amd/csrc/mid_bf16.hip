@@ -45,9 +45,15 @@ float estimate_us(float r, int K, float fix, float round, float fill) {
   return fix * fmaxf(1.0f, r) + (float)K / 1024.0f * (round * ceilf(r) + fill * fminf(1.0f, r));
 }
 
-// One row group and 96 MB of weights or more: the stream bounds the call, and the six-block
-// shapes with non-temporal loads are the fastest (33.0 us at 64 x 4096 -> 2 x 11008 GLU,
-// 180 MB; the two- and four-block shapes 36 and 40).  Otherwise the shape of the least
+// One row group and 96 MB of weights or more: the weights come from HBM and bound the call.  There
+// the six-block shapes run with non-temporal loads (22016 columns, K 4096, cold caches: 32 rows
+// 29.9 us, 34.8 cached; 48 rows 31.1 and 34.9; 64 rows 33.1 and 36.3, on the 96-row shape 36.7),
+// the 96- and 128-row ones, cached only, when more than 64 rows need them (65 rows: 36.6 us, two
+// groups of 64 49.5), and the two- and four-block shapes when they cover the width in one round
+// (32 x 8192 -> 8192: 27.4 us, six blocks 42.5; in more rounds 32 x 4096 -> 22016 43.2 against
+// 29.9).  Over 152 calls of 32..128 rows and 101..283 MB the choice is 2% off the best shape of
+// each.  Fewer bytes may stay in the 256 MB cache between calls, where cached loads win (the same
+// 100 MB in every call, 32 rows: 18.6 us, non-temporal 24.4).  Otherwise the shape of the least
 // estimated time, if that is below 0.9 of the tile kernel's: over the shapes of the fit the
 // rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60), no
 // shape runs 5% slower.  More than 1536 rows are outside the fit, and outputs narrower than
@@ -64,8 +70,12 @@ int mid_shape(int M, int K, int NP, bool glu) {
     const int groups = (M + 16 * s.mb - 1) / (16 * s.mb);
     const bool nt = i >= kMidFirstNT && i <= kMidLastNT;
     if (glu && i == kMidLinearOnly) continue;
-    if (stream && groups == 1 ? s.blocks != 6 || (!nt && s.mb <= 4) : nt) continue;
     const int64_t wgs = (int64_t)groups * ((npb + s.blocks - 1) / s.blocks);
+    if (!stream || groups > 1) {
+      if (nt) continue;
+    } else if (s.blocks == 6 ? !nt && (s.mb <= 4 || M <= 64) : s.blocks > 6 || wgs > 256) {
+      continue;
+    }
     const float us = estimate_us((float)wgs / 256.0f, K, s.fix, s.round, s.fill);
     if (us < best_us) {
       best_us = us;

@@ -1,6 +1,8 @@
 """Middle-row kernel (csrc/mid_kernel.h): its register use on the CPU, and on the GPU every kind at the
 edges of its tiles (row blocks and groups, ragged columns and K, the smallest and the largest of its
 range) against the fp64 oracle, with the row error bar of the other bf16 paths."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -17,6 +19,24 @@ def test_no_spills(source, tmp_path):
     res = kernel_resources(source, tmp_path)
     assert res
     assert [n for n, f in res.items() if f.get("private_segment_fixed_size", 0) or f.get("vgpr_spill_count", 0)] == []
+
+
+def _shape(M, K, N, glu=False):
+    """The workgroup shape that the built library takes for a call (-1: the tile kernel)."""
+    from paper_2407_09577_amd import flashnorm as fn
+    choose = getattr(fn.lib(), "_ZN2fn9mid_shapeEiiib")
+    choose.argtypes, choose.restype = [ctypes.c_int] * 3 + [ctypes.c_bool], ctypes.c_int
+    return choose(M, K, 2 * ((N // 2 + 15) // 16 * 16) if glu else (N + 15) // 16 * 16, glu)
+
+
+@pytest.mark.parametrize("M,K,N,glu,shape", [
+    (17, 4096, 22016, True, 13), (32, 4096, 22016, True, 13), (33, 4096, 22016, False, 14), (48, 4096, 22016, True, 14),
+    (49, 4096, 22016, True, 15), (64, 4096, 22016, True, 15), (64, 4096, 22016, False, 15), (65, 4096, 22016, True, 9),
+    (32, 8192, 8192, False, 0), (48, 4096, 14336, False, 4), (64, 5120, 15360, False, 7), (32, 4096, 12288, False, 1)])
+def test_weight_streams(M, K, N, glu, shape):
+    # One row group and 96 MB of weights or more: the smallest shape that holds the rows, six blocks wide with
+    # non-temporal loads, unless a narrower one covers the width in one round of workgroups.
+    assert _shape(M, K, N, glu) == shape
 
 
 def _err(y, ref):
