@@ -46,13 +46,13 @@ float estimate_us(float r, int K, float fix, float round, float fill) {
 }
 
 // One row group and 96 MB of weights or more: the weights come from HBM and bound the call.  There
-// the six-block shapes run with non-temporal loads (22016 columns, K 4096, cold caches: 32 rows
-// 29.9 us, 34.8 cached; 48 rows 31.1 and 34.9; 64 rows 33.1 and 36.3, on the 96-row shape 36.7),
-// the 96- and 128-row ones, cached only, when more than 64 rows need them (65 rows: 36.6 us, two
-// groups of 64 49.5), and the two- and four-block shapes when they cover the width in one round
-// (32 x 8192 -> 8192: 27.4 us, six blocks 42.5; in more rounds 32 x 4096 -> 22016 43.2 against
-// 29.9).  Over 152 calls of 32..128 rows and 101..283 MB the choice is 2% off the best shape of
-// each.  Fewer bytes may stay in the 256 MB cache between calls, where cached loads win (the same
+// the six-block shapes run with non-temporal loads (22016 columns, K 4096, caches cold: 32 rows
+// 30.1 us, 31.4 cached; 48 rows 31.2 and 31.3; 64 rows 33.2 and 33.3), the 96- and 128-row ones,
+// cached only, when more than 64 rows need them (65 rows: 33.6 us, two groups of 64 47.5), and the
+// two- and four-block shapes when they cover the width in one round (32 x 8192 -> 8192: 25.3 us,
+// six blocks 42.6; in two rounds 32 x 4096 -> 22016 40.0 against 30.1).  Over 152 calls of 32..128
+// rows and 101..283 MB the choice is 2% off the best shape of each and never behind the tiles.
+// Fewer bytes may stay in the 256 MB cache between calls, where cached loads win (the same
 // 100 MB in every call, 32 rows: 18.6 us, non-temporal 24.4).  Otherwise the shape of the least
 // estimated time, if that is below 0.9 of the tile kernel's: over the shapes of the fit the
 // rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60), no
