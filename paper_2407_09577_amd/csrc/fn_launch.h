@@ -71,6 +71,8 @@ int mid_shape(int M, int K, int NP, bool glu);
 hipError_t launch_mid_bf16(const PrefillArgs& p, int shape);
 // Estimated time of the many-row kernel's automatic tiles, us on MI355X.
 float prefill_estimate_us(int M, int K, int NP, bool glu);
+// True where those are 256 x 256 (at least one per compute unit), else they have 128 rows.
+bool prefill_fills_256x256(int M, int NP);
 float estimate_us(float r, int K, float fix, float round, float fill);
 
 struct DecodeArgs {

@@ -55,14 +55,29 @@ float estimate_us(float r, int K, float fix, float round, float fill) {
 // Fewer bytes may stay in the 256 MB cache between calls, where cached loads win (the same
 // 100 MB in every call, 32 rows: 18.6 us, non-temporal 24.4).  Otherwise the shape of the least
 // estimated time, if that is below 0.9 of the tile kernel's: over the shapes of the fit the
-// rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60), no
-// shape runs 5% slower.  More than 1536 rows are outside the fit, and outputs narrower than
-// 256 packed columns keep the tiles' one chain of sums over K (the automatic tile there is
-// bitwise the forced one).
+// rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60).  More
+// than 1536 rows are outside the fit, and outputs narrower than 256 packed columns keep the tiles'
+// one chain of sums over K (the automatic tile there is bitwise the forced one).
+//
+// Below the fit's least K the estimates miss what a call is made of: prologue, epilogue and the
+// output's stores.  A second round pays the fixed part again; so do the 12- and 16-block shapes at
+// any K, as their LDS leaves a compute unit room for one workgroup (1392 x 744 -> 2 x 8904 with
+// 770 of them: 65.8 us, the tiles 55.3).  Nothing hides those wide shapes' epilogue: at short K
+// they compete only in three rounds (two below K = 64) and only where the tiles would be 256 x 256
+// (532 x 64 -> 17822: 17.1 us, 128-row tiles 9.6; 797 x 128 -> 19542: 21.0, 256-row tiles 28.5;
+// 1527 x 16 -> 2 x 10143 in four rounds: 31.7 and 22.9).
+//
+// Held to the tiles on 3000 fresh random shapes, the rule takes 0.83 of their time at K 8..511
+// (1000 shapes; 0.6% run over 5% slower, at worst 14%: 1155 x 296 -> 17958, 36.5 us and 32.2) and
+// 0.61 at K 512..8192 (2000; 0.4%, at worst 13%: 130 x 4544 -> 12494, 47.6 and 42.2).  The
+// estimates alone ran 11.5% of the short ones over 5% slower, at worst 94%.
+constexpr int kMidFitMinK = 512;
+
 int mid_shape(int M, int K, int NP, bool glu) {
   if (M > kMidMaxM || NP < 256) return -1;
   const int npb = NP / 16;
   const bool stream = (int64_t)K * NP * 2 >= 96 * 1000 * 1000;
+  const bool big = prefill_fills_256x256(M, NP);
   int best = -1;
   float best_us = 0.9f * prefill_estimate_us(M, K, NP, glu);
   for (int i = 0; i < kMidShapeCount; ++i) {
@@ -76,7 +91,11 @@ int mid_shape(int M, int K, int NP, bool glu) {
     } else if (s.blocks == 6 ? !nt && (s.mb <= 4 || M <= 64) : s.blocks > 6 || wgs > 256) {
       continue;
     }
-    const float us = estimate_us((float)wgs / 256.0f, K, s.fix, s.round, s.fill);
+    const bool wide = s.blocks > 8;
+    const float r = (float)wgs / 256.0f;
+    if (wide && K < kMidFitMinK && (!big || r > (K < 64 ? 2.0f : 3.0f))) continue;
+    float us = estimate_us(r, K, s.fix, s.round, s.fill);
+    if (K < kMidFitMinK || wide) us += s.fix * (ceilf(r) - fmaxf(1.0f, r));
     if (us < best_us) {
       best_us = us;
       best = i;

@@ -859,10 +859,11 @@ static hipError_t launch_auto_cfg(const PrefillArgs& p) {
 // yields at least one tile per compute unit.  Otherwise 128-row tiles with 8 waves, 128 or 96 columns wide, whichever
 // fills the 256 compute units best (whole rounds of tiles); 96 is not used for a
 // GLU, whose wave tiles must hold whole gate/up block pairs.
+constexpr int kCUs = 256;
+bool prefill_fills_256x256(int M, int NP) { return ((int64_t)(M + 255) / 256) * ((NP + 255) / 256) >= kCUs; }
+
 static int auto_tile(int M, int NP, bool glu) {
-  constexpr int kCUs = 256;
-  const int64_t big = ((int64_t)(M + 255) / 256) * ((NP + 255) / 256);
-  if (big >= kCUs) return TILE_256x256_W8_PF_SP;
+  if (prefill_fills_256x256(M, NP)) return TILE_256x256_W8_PF_SP;
   if (glu) return TILE_128x128_W8T;
   const int64_t t128 = ((int64_t)(M + 127) / 128) * ((NP + 127) / 128);
   const int64_t t96 = ((int64_t)(M + 127) / 128) * ((NP + 95) / 96);

@@ -32,10 +32,20 @@ def _shape(M, K, N, glu=False):
 @pytest.mark.parametrize("M,K,N,glu,shape", [
     (17, 4096, 22016, True, 13), (32, 4096, 22016, True, 13), (33, 4096, 22016, False, 14), (48, 4096, 22016, True, 14),
     (49, 4096, 22016, True, 15), (64, 4096, 22016, True, 15), (64, 4096, 22016, False, 15), (65, 4096, 22016, True, 9),
-    (32, 8192, 8192, False, 0), (48, 4096, 14336, False, 4), (64, 5120, 15360, False, 7), (32, 4096, 12288, False, 1)])
+    (32, 8192, 8192, False, 0), (48, 4096, 14336, False, 4), (64, 5120, 15360, False, 7), (32, 4096, 12288, False, 1),
+    (17, 7616, 16384, False, 1)])
 def test_weight_streams(M, K, N, glu, shape):
     # One row group and 96 MB of weights or more: the smallest shape that holds the rows, six blocks wide with
     # non-temporal loads, unless a narrower one covers the width in one round of workgroups.
+    assert _shape(M, K, N, glu) == shape
+
+
+@pytest.mark.parametrize("M,K,N,glu,shape", [
+    (532, 64, 17822, False, -1), (675, 64, 9498, False, -1), (1030, 192, 9090, True, -1), (737, 312, 16450, False, -1), (1527, 16, 20286, True, -1),
+    (1306, 256, 3901, False, -1), (1392, 744, 17808, True, -1), (797, 128, 19542, False, 10), (747, 152, 2216, False, 16),
+    (23, 64, 16953, False, 2), (333, 4096, 12288, False, 17)])
+def test_short_depths(M, K, N, glu, shape):
+    # The kernel that is faster where the fixed part of every round and the output's stores make up the call.
     assert _shape(M, K, N, glu) == shape
 
 
