@@ -721,14 +721,20 @@ __global__ __launch_bounds__(64 * KS, 1) void f32_mfma_kernel(const float* __res
 //
 // Automatic (2222 random shapes of 1..2048 rows, K 64..4096, 8..8192 columns, linear and GLU,
 // on MI355X): the few-row kernel when 16 x 64 tiles would be 32 or fewer (its narrow tiles
-// spread them over more units: 16 x 576 -> 576 6.1 us, 7.0 on the matrix cores), and for one or
-// two rows of up to 64 tiles (1 x 332 -> 4084: 5.5 and 6.6).  Otherwise the matrix-core kernel:
+// spread them over more units: 16 x 576 -> 576 6.1 us, 7.0 on the matrix cores), for one or
+// two rows of up to 64 tiles (1 x 332 -> 4084: 5.5 and 6.6), and for up to 64 tiles of at most 16
+// columns from K = 256 on (its 4-column tiles still fit one round, and three quarters of a 64-column
+// tile would be padding: 958 x 2380 -> 6 9.4 us, 15.1 on the matrix cores; from 65 tiles, or 17
+// columns, on those are the faster; of a GLU's 32 packed columns only where the rows' pitch is an
+// odd number of 16 bytes, which splits the 64 bytes that the matrix-core kernel loads of a row:
+// 731 x 2052 -> 2 x 4 10.9 and 13.1 us, at K = 2048 the other way by 2%).  Otherwise the
+// matrix-core kernel:
 // 32-row tiles with four waves from 384 tiles on (1024 x 2048 -> 4096: 146 us, 170 with 16
 // rows), else 16-row tiles, with four waves from 128 tiles and eight below (64 x 2048 -> 2048:
-// 14.3 us, 14.9 with four).  The choice takes 0.51 of the time of the vector kernels it
-// replaces (geometric mean; 500 x 2048 -> 2048: 165 -> 41 us, 16 x 2048 -> 8192: 162 -> 15), no
-// shape is 8% slower, and the error against fp64 is at most theirs: a chain of sums is
-// K / 64 (32 rows: K / 32) ops long and shorter with eight waves.
+// 14.3 us, 14.9 with four).  500 x 2048 -> 2048: 163 us on the vector kernels, 38.7 so;
+// 16 x 2048 -> 8192: 162 and 15.  Over 1500 fresh shapes the choice takes 0.74 of the vector
+// kernels' time, three run over 5% slower, at worst 10% (580 x 3772 -> 27).  The error against fp64 is at most the vector kernels': a chain of
+// sums is K / 64 (32 rows: K / 32) ops long and shorter with eight waves.
 
 template <int EPI, bool GS, int MB, int KS>
 static void launch_f32_mfma(const F32Args& p) {
@@ -742,7 +748,9 @@ static hipError_t launch_f32_epi(const F32Args& p) {
   int cfg = p.cfg;
   if (cfg == 0) {
     const int64_t nt = (p.NP + 63) / 64, tiles = nt * ((p.M + 15) / 16);
-    if (tiles <= 32 || (p.M <= 2 && nt <= 64)) {
+    const bool sliver = tiles <= 64 && p.K >= 256 &&
+                        (epi_is_glu(EPI) ? p.NP == 32 && p.lda % 8 : p.NP == 16 && EPI != EPI_HEADNORM);
+    if (tiles <= 32 || (p.M <= 2 && nt <= 64) || sliver) {
       cfg = 3;
     } else if (p.M > 65535 * 16) {  // more 16-row tiles than a grid dimension holds
       cfg = 1;

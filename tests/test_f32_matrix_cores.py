@@ -93,3 +93,19 @@ def test_rotation_and_head_norms(M, Hq, Hkv, h):
     nrm[:, Hq + Hkv:] = heads[:, Hq + Hkv:] * s[:, None]
     ref = nrm.flatten(1)
     assert float(((z.double() - ref).abs().amax(1) / ref.abs().amax(1)).max()) <= 1e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(520, 256, 16), (958, 2380, 6), (1024, 1024, 1), (1009, 516, 11)])
+def test_slivers_take_the_few_row_kernel(M, K, N):
+    # Outputs of at most 16 columns, 33 to 64 row tiles: the few-row kernel's bits (configuration 3).
+    from paper_2407_09577_amd import flashnorm as fn
+    w = workloads.make("linear", M, K, N, dtype=torch.float32, eps=1e-5, seed=M)
+    Ws, _, _ = fn.fold_weights(w.W.cuda(), w.g.cuda())
+    a = w.a.cuda()
+    assert torch.equal(fn.flashnorm_linear(a, Ws, N, w.eps), fn.flashnorm_linear(a, Ws, N, w.eps, path=3 << 8))
+    # A GLU of at most 16 features, where the rows' pitch is an odd number of 16 bytes.
+    g = workloads.make("glu", M, 516, N, dtype=torch.float32, eps=1e-5, seed=N)
+    Wg, _, _ = fn.fold_weights(g.W.cuda(), g.g.cuda(), layout=fn.FN_LAYOUT_GLU)
+    a = g.a.cuda()
+    assert torch.equal(fn.flashnorm_glu(a, Wg, N, g.eps), fn.flashnorm_glu(a, Wg, N, g.eps, path=3 << 8))
