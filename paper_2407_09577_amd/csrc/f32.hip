@@ -1,8 +1,8 @@
 // fp32 fused norm-then-project kernels (exact fp32 products, no reduced-precision matrix-core
-// modes): two on the vector units, and one on the fp32 matrix cores for all but the smallest
-// calls.
+// modes): one on the fp32 matrix cores for all but the smallest calls, one on the vector units for
+// those, and vector tiles that a caller can name.
 //
-// f32_kernel.  A workgroup owns a BM x 64 output tile (BM = 16 RI rows) and KS groups of 256
+// f32_kernel, the vector tiles (named configurations 1 and 2 alone).  A workgroup owns a BM x 64 output tile (BM = 16 RI rows) and KS groups of 256
 // threads split K between them: group g takes the 64-deep k steps g, g + KS, ...,
 // staging its activation and weight tiles in its own LDS buffers.  The threads
 // that stage an activation row also accumulate its sum of squares (and sum, for
@@ -164,11 +164,10 @@ __device__ __forceinline__ void f32_epilogue(float (&acc)[RI][NJ], const StatT<E
   }
 }
 
-template <int EPI, bool GS, int RI, int KS>
+template <int EPI, int RI, int KS>
 __global__ __launch_bounds__(256 * KS) void f32_kernel(const float* __restrict__ a, int M, int K, int lda,
-                                                       const float* __restrict__ ws, int NP, int KP,
-                                                       int ncols, float* __restrict__ y, int ldy,
-                                                       EpiArgs ep) {
+                                                       const float* __restrict__ ws, int NP, int ncols,
+                                                       float* __restrict__ y, int ldy, EpiArgs ep) {
   constexpr int BM = 16 * RI, BN = 64, BK = 64;
   constexpr int TPR = 256 / BM;            // staging threads per activation row
   constexpr int QA = BK / (4 * TPR);       // activation quads per staging thread and step (= RI)
@@ -236,16 +235,6 @@ __global__ __launch_bounds__(256 * KS) void f32_kernel(const float* __restrict__
         ss = fmaf(av[q].y, av[q].y, ss);
         ss = fmaf(av[q].z, av[q].z, ss);
         ss = fmaf(av[q].w, av[q].w, ss);
-      }
-      if constexpr (GS) {  // run-time g (unfolded W): a_k g_k in fp32
-        const int k = k0 + lkq + 4 * TPR * q;
-        if (lr_ok && k < K) {
-          const float4 gv = *reinterpret_cast<const float4*>(ep.g_rt + k);
-          av[q].x *= gv.x;
-          av[q].y *= gv.y;
-          av[q].z *= gv.z;
-          av[q].w *= gv.w;
-        }
       }
     }
     __syncthreads();
@@ -577,8 +566,11 @@ __global__ __launch_bounds__(64 * KS, 1) void f32_mfma_kernel(const float* __res
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (NP + 63) / 64;
+  const int64_t bid = blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
+  if (bid >= (int64_t)tiles_m * tiles_n) return;  // the last row of a grid of more than kF32GridX tiles
   int tm, tn;
-  tile_of_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y, gridDim.y, gridDim.x, tm, tn);
+  tile_of_block((int)bid, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, p0 = tn * 64;
   const int r = lane & 15, q = lane >> 4;
   const int rows = min(BM, M - m0);
@@ -716,8 +708,8 @@ __global__ __launch_bounds__(64 * KS, 1) void f32_mfma_kernel(const float* __res
   f32_epilogue<EPI, RI, 4>(out, rss, rsa, tx, ty, m0 + 16 * grp * RI, p0, M, ncols, y, ldy, ep, tn == 0);
 }
 
-// Tile configurations (kF32CfgCount): 0 automatic, 1 = 64-row tiles with one k group,
-// 2 = 16-row tiles of 64 columns with four k groups, 3 = the few-row kernel.
+// Tile configurations (kF32CfgCount): 0 automatic; by name, 1 = 64-row vector tiles with one k
+// group, 2 = 16-row vector tiles of 64 columns with four k groups, 3 = the few-row kernel.
 //
 // Automatic (2222 random shapes of 1..2048 rows, K 64..4096, 8..8192 columns, linear and GLU,
 // on MI355X): the few-row kernel when 16 x 64 tiles would be 32 or fewer (its narrow tiles
@@ -736,11 +728,18 @@ __global__ __launch_bounds__(64 * KS, 1) void f32_mfma_kernel(const float* __res
 // kernels' time, three run over 5% slower, at worst 10% (580 x 3772 -> 27).  The error against fp64 is at most the vector kernels': a chain of
 // sums is K / 64 (32 rows: K / 32) ops long and shorter with eight waves.
 
+// Workgroups along x of a matrix-core grid (times 512 threads stays below 2^32); more go along y.
+constexpr int64_t kF32GridX = 1 << 22;
+
 template <int EPI, bool GS, int MB, int KS>
-static void launch_f32_mfma(const F32Args& p) {
-  dim3 grid((p.NP + 63) / 64, (p.M + 16 * MB - 1) / (16 * MB));
+static hipError_t launch_f32_mfma(const F32Args& p) {
+  const int64_t tiles = (int64_t)((p.NP + 63) / 64) * ((p.M + 16 * MB - 1) / (16 * MB));
+  if (tiles > INT32_MAX) return hipErrorInvalidValue;
+  const int64_t gx = tiles < kF32GridX ? tiles : kF32GridX;
+  const dim3 grid((unsigned)gx, (unsigned)((tiles + gx - 1) / gx));
   hipLaunchKernelGGL((f32_mfma_kernel<EPI, GS, MB, KS>), grid, dim3(64 * KS), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
                      p.NP, p.KP, p.ncols, p.y, p.ldy, p.ep);
+  return hipGetLastError();
 }
 
 template <int EPI, bool GS = false>
@@ -752,23 +751,27 @@ static hipError_t launch_f32_epi(const F32Args& p) {
                         (epi_is_glu(EPI) ? p.NP == 32 && p.lda % 8 : p.NP == 16 && EPI != EPI_HEADNORM);
     if (tiles <= 32 || (p.M <= 2 && nt <= 64) || sliver) {
       cfg = 3;
-    } else if (p.M > 65535 * 16) {  // more 16-row tiles than a grid dimension holds
-      cfg = 1;
+    } else if (nt * ((p.M + 31) / 32) >= 384) {
+      return launch_f32_mfma<EPI, GS, 2, 4>(p);
     } else {
-      if (nt * ((p.M + 31) / 32) >= 384) launch_f32_mfma<EPI, GS, 2, 4>(p);
-      else if (tiles >= 128) launch_f32_mfma<EPI, GS, 1, 4>(p);
-      else launch_f32_mfma<EPI, GS, 1, 8>(p);
-      return hipGetLastError();
+      return tiles >= 128 ? launch_f32_mfma<EPI, GS, 1, 4>(p) : launch_f32_mfma<EPI, GS, 1, 8>(p);
     }
   }
-  if (cfg == 1) {
-    dim3 grid((p.NP + 63) / 64, (p.M + 63) / 64);
-    hipLaunchKernelGGL((f32_kernel<EPI, GS, 4, 1>), grid, dim3(256), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
-                       p.NP, p.KP, p.ncols, p.y, p.ldy, p.ep);
-  } else if (cfg == 2) {
-    dim3 grid((p.NP + 63) / 64, (p.M + 15) / 16);
-    hipLaunchKernelGGL((f32_kernel<EPI, GS, 1, 4>), grid, dim3(1024), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
-                       p.NP, p.KP, p.ncols, p.y, p.ldy, p.ep);
+  if (cfg == 1 || cfg == 2) {
+    // Only the core kinds can name a configuration (the others return FN_ERR_UNSUPPORTED for one).
+    if constexpr (EPI < EPI_REGLU && !GS) {
+      if (cfg == 1) {
+        dim3 grid((p.NP + 63) / 64, (p.M + 63) / 64);
+        hipLaunchKernelGGL((f32_kernel<EPI, 4, 1>), grid, dim3(256), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
+                           p.NP, p.ncols, p.y, p.ldy, p.ep);
+      } else {
+        dim3 grid((p.NP + 63) / 64, (p.M + 15) / 16);
+        hipLaunchKernelGGL((f32_kernel<EPI, 1, 4>), grid, dim3(1024), 0, p.stream, p.a, p.M, p.K, p.lda, p.ws,
+                           p.NP, p.ncols, p.y, p.ldy, p.ep);
+      }
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else {
     // Column quads per tile: the widest of 4, 2, 1 that still makes FEW_MIN_WG workgroups.
     const int64_t mt = (p.M + 15) / 16;

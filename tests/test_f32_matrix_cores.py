@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from _codeobj import kernel_resources
+from _codeobj import kernel_resources, template_args
 from paper_2407_09577_amd import workloads
 
 TOL = 1e-5  # row-normwise: fp32 products and chains of at most K / 32 sums
@@ -16,6 +16,13 @@ def test_no_spills(tmp_path):
     res = {n: f for n, f in kernel_resources("f32.hip", tmp_path).items() if "f32_mfma_kernel" in n}
     assert res
     assert [n for n, f in res.items() if f.get("private_segment_fixed_size", 0) or f.get("vgpr_spill_count", 0)] == []
+
+
+def test_vector_tiles_are_built_for_the_kinds_that_can_name_them(tmp_path):
+    # f32_kernel is reached by a named configuration alone: linear, GLU, LayerNorm and the two baseline kinds,
+    # without run-time g, in its two tile sizes.
+    got = sorted(template_args(n) for n in kernel_resources("f32.hip", tmp_path) if "10f32_kernel" in n)
+    assert got == sorted([epi, ri, 5 - ri] for epi in range(5) for ri in (1, 4))
 
 
 def _err(y, ref):
@@ -109,3 +116,45 @@ def test_slivers_take_the_few_row_kernel(M, K, N):
     Wg, _, _ = fn.fold_weights(g.W.cuda(), g.g.cuda(), layout=fn.FN_LAYOUT_GLU)
     a = g.a.cuda()
     assert torch.equal(fn.flashnorm_glu(a, Wg, N, g.eps), fn.flashnorm_glu(a, Wg, N, g.eps, path=3 << 8))
+
+
+@pytest.mark.gpu
+def test_more_row_tiles_than_a_grid_dimension():
+    # 65536 tiles of 16 rows and a remainder: every kind that has no configuration to name.
+    from paper_2407_09577_amd import flashnorm as fn
+    M, K = 65536 * 16 + 5, 8
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.randn(M, K, generator=gen, device="cuda")
+    g = torch.rand(K, generator=gen, device="cuda") + 0.5
+    inv = torch.empty(M, device="cuda")
+    x = a.double()
+    s = (1e-5 + x.square().mean(1, keepdim=True)).rsqrt()
+
+    def weight(N, use_g):
+        W = torch.randn(K, N, generator=gen, device="cuda") * K ** -0.5
+        return fn.fold_weights(W, g if use_g else None)[0], (x * g.double()) @ W.double()
+
+    def err(y, ref):
+        assert bool(torch.isfinite(y).all())
+        return float(((y.double() - ref).abs().amax(1) / ref.abs().amax(1).clamp(min=1e-3)).max())
+
+    Wp, t = weight(20, False)
+    assert err(fn.flashnorm_linear_unfolded(a, g, Wp, 20, 1e-5), t * s) <= TOL
+    Ws, t = weight(20, True)
+    assert err(fn.flashnorm_linear_relu(a, Ws, 20, 1e-5, inv), t.clamp(min=0)) <= TOL
+    assert float((inv.double() / s[:, 0] - 1).abs().max()) <= TOL
+    pos = torch.arange(M, device="cuda", dtype=torch.int32) % 512
+    cos, sin = (v.cuda() for v in workloads.rope_tables(512, 4))
+    Ws, t = weight(12, True)
+    p = (t * s)[:, :8].reshape(M, 2, 2, 2)
+    c, d = cos.double()[pos.long()][:, None], sin.double()[pos.long()][:, None]
+    r = torch.stack((p[..., 0] * c - p[..., 1] * d, p[..., 0] * d + p[..., 1] * c), -1).flatten(1)
+    r[:, :4] *= 0.5
+    y = fn.flashnorm_qkv_rope(a, Ws, 1, 1, 4, 1e-5, pos, cos, sin, 0.5)
+    assert err(y, torch.cat((r, (t * s)[:, 8:]), 1)) <= TOL
+    Ws, t = weight(24, True)
+    one = torch.ones(8, device="cuda")
+    h = t.reshape(M, 3, 8)
+    n = h / (1e-5 + h.square().mean(2, keepdim=True)).sqrt()
+    y = fn.flashnorm_qkv_headnorm(a, Ws, 1, 1, 8, 1e-5, one, one, one, 1e-5)
+    assert err(y, n.flatten(1)) <= TOL
