@@ -113,7 +113,8 @@ size_t fold_weights_size(int64_t K, int64_t N, int layout, int ws_dtype);
  *           of the deferred LayerNorm), accumulated in fp64 and rounded once.
  *   c_star  optional [N] fp32: sum over k of beta_k W[k,n] with the unfolded W,
  *           accumulated in fp64 and rounded once; requires beta.
- *   colsum and c_star are available for FN_LAYOUT_LINEAR only. */
+ *   colsum and c_star are available for FN_LAYOUT_LINEAR only.  They may be written over g,
+ *   and colsum alone (without c_star) over W. */
 int fold_weights(const void* W, int64_t stride_k, int64_t stride_n, int w_dtype, const float* g,
                  const float* beta, int64_t K, int64_t N, int layout, void* W_star, int ws_dtype,
                  float* colsum, float* c_star, void* stream);

@@ -163,15 +163,18 @@ __global__ __launch_bounds__(256) void fold_pack_bf16_kernel(const T* __restrict
 }
 
 // LayerNorm's sums over K of a linear layout (packed column == logical column), with the bf16
-// packing done on the way (PACK) or alone for fp32 storage.  A block owns 16 columns and all of
+// packing done on the way (kSumsPack) or alone for fp32 storage.  A block owns 16 columns and all of
 // K, its 16 waves take k blocks w, w + 16, ...: every lane sums eight k of a column in fp64,
 // then lanes and waves are added in a fixed order that does not depend on the strides.  (One
 // thread per column, K steps in series on N / 128 blocks, took 1358 us at 4096 x 4096 beside
-// the packing; both together 22.3 us from [N, K] and 25 us from [K, N].)
-template <typename T, bool PACK>
+// the packing; both together 21.2 us from [N, K] and 25 us from [K, N].)
+// kSumsAfter: the packing is done and the sums read it back, for sums written over g or W, which
+// no block may still be reading.
+enum FoldSums { kSumsPack, kSumsAlone, kSumsAfter };
+template <typename T, FoldSums MODE>
 __global__ __launch_bounds__(1024) void fold_sums_kernel(const T* __restrict__ W, FoldIn in, int NPB, int KB,
                                                          u32x4* __restrict__ out, float* __restrict__ colsum,
-                                                         float* __restrict__ cstar) {
+                                                         float* __restrict__ cstar, int ws_dtype) {
   __shared__ double part[2][16][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Neighbouring column blocks (which share W's lines when its rows are contiguous) on one XCD.
@@ -183,9 +186,18 @@ __global__ __launch_bounds__(1024) void fold_sums_kernel(const T* __restrict__ W
   for (int kb = wave; kb < KB; kb += 16) {
     const int64_t k0 = (int64_t)kb * kKB + (lane >> 4) * 8;
     float w[8], g[8], b[8];
-    load_k8(W, in.sk, in.sn, k0, n, in.K, in.vec, w);
-    load_v8(in.g, k0, in.K, in.gvec, 1.0f, g);
-    if constexpr (PACK) {
+    if (MODE != kSumsAfter || cstar) load_k8(W, in.sk, in.sn, k0, n, in.K, in.vec, w);
+    if constexpr (MODE != kSumsAfter) load_v8(in.g, k0, in.K, in.gvec, 1.0f, g);
+    if constexpr (MODE == kSumsAfter) {
+      if (ws_dtype == kDtypeBf16) {
+        const u32x4 h = out[((int64_t)kb * NPB + cb) * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cs += (double)bf16_lo(h[i]) + (double)bf16_hi(h[i]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cs += (double)reinterpret_cast<const float*>(out)[(k0 + e) * 16 * NPB + col];
+      }
+    } else if constexpr (MODE == kSumsPack) {
       const u32x4 h = fold8_bf16(g, w, n >= 0);
       out[((int64_t)kb * NPB + cb) * 64 + lane] = h;
 #pragma unroll
@@ -292,12 +304,20 @@ static hipError_t launch_fold_t(const FoldArgs& p) {
   const int NPB = (int)(NP / 16), KB = (int)(KP / kKB);
   u32x4* out = reinterpret_cast<u32x4*>(p.ws);
   const bool sums = p.colsum || p.cstar;
+  auto launch_sums = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(NPB), dim3(1024), 0, p.stream, W, in, NPB, KB, out, p.colsum, p.cstar, p.ws_dtype);
+    return hipGetLastError();
+  };
+  // Sums over g, or over W where c* does not need it, wait for the packing.
+  auto over = [&](const float* s, const void* q, int64_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(s), b = reinterpret_cast<uintptr_t>(q);
+    return s && q && a < b + (uintptr_t)bytes && b < a + (uintptr_t)p.N * 4;
+  };
+  const int64_t wbytes = ((p.K - 1) * p.sk + (p.N - 1) * p.sn + 1) * (int64_t)sizeof(T);
+  const bool after = over(p.colsum, p.g, p.K * 4) || over(p.cstar, p.g, p.K * 4) ||
+                     (!p.cstar && over(p.colsum, p.W, wbytes));
   if (p.ws_dtype == kDtypeBf16) {
-    if (sums) {
-      hipLaunchKernelGGL((fold_sums_kernel<T, true>), dim3(NPB), dim3(1024), 0, p.stream, W, in, NPB, KB, out,
-                         p.colsum, p.cstar);
-      return hipGetLastError();
-    }
+    if (sums && !after) return launch_sums(fold_sums_kernel<T, kSumsPack>);
     // Four fragments per wave once that leaves two waves per SIMD (2048); below, one (576 x 1536:
     // 3.6 us with one, 7.1 with four).
     auto go = [&](auto kernel, int nf) {
@@ -308,16 +328,15 @@ static hipError_t launch_fold_t(const FoldArgs& p) {
     };
     if ((int64_t)KB * NPB >= 4 * 2048) go(fold_pack_bf16_kernel<T, 4>, 4);
     else go(fold_pack_bf16_kernel<T, 1>, 1);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || !sums ? e : launch_sums(fold_sums_kernel<T, kSumsAfter>);
   }
   const int ptiles = (int)((NP + 63) / 64);
   hipLaunchKernelGGL(fold_pack_f32_kernel<T>, dim3((unsigned)(KP / 32) * ptiles), dim3(256), 0, p.stream, W, in, KP,
                      NP, ptiles, reinterpret_cast<float*>(p.ws));
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !sums) return e;
-  hipLaunchKernelGGL((fold_sums_kernel<T, false>), dim3(NPB), dim3(1024), 0, p.stream, W, in, NPB, KB, nullptr,
-                     p.colsum, p.cstar);
-  return hipGetLastError();
+  return after ? launch_sums(fold_sums_kernel<T, kSumsAfter>) : launch_sums(fold_sums_kernel<T, kSumsAlone>);
 }
 
 hipError_t launch_fold(const FoldArgs& p) {

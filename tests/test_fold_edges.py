@@ -109,3 +109,36 @@ def test_padding_is_positive_zero(ws, K, N, sums):
         assert bits.shape[1] >= N
         assert not bits[K:].any() and not bits[:, N:].any(), name
         assert bits[:K, :N].any(), name
+
+
+@pytest.mark.parametrize("src,ws", [(torch.bfloat16, torch.bfloat16), (torch.float32, torch.bfloat16),
+                                    (torch.float32, torch.float32), (torch.bfloat16, torch.float32)])
+@pytest.mark.parametrize("K,N,transposed", [(4160, 2000, True), (200, 72, False)])
+def test_sums_over_the_inputs(src, ws, K, N, transposed):
+    """colsum and c_star may take g's memory, and colsum alone W's: both are read before they are written."""
+    from paper_2407_09577_amd import flashnorm as fn
+    gen = torch.Generator().manual_seed(K)
+    W = (torch.randn(K, N, generator=gen) * K ** -0.5).to(src).cuda()
+    W = W.t().contiguous().t() if transposed else W
+    g, beta = (torch.rand(K, generator=gen) + 0.5).cuda(), torch.randn(K, generator=gen).cuda()
+    Ws, cs, cb = fn.fold_weights(W, g, beta=beta, colsum=True, c_star=True, ws_dtype=ws)
+
+    def fold(W_, g_, colsum, c_star):
+        out = torch.empty_like(Ws)
+        rc = fn.lib().fold_weights(W_.data_ptr(), W_.stride(0), W_.stride(1), fn._dt(W_), g_.data_ptr(), beta.data_ptr(),
+                                   K, N, fn.FN_LAYOUT_LINEAR, out.data_ptr(),
+                                   fn.FN_BF16 if ws == torch.bfloat16 else fn.FN_F32, colsum, c_star,
+                                   torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        return out
+
+    over = g.clone()
+    assert torch.equal(fold(W, over, over.data_ptr(), over.data_ptr() + 4 * N), Ws)
+    assert torch.equal(over[:N], cs) and torch.equal(over[N:2 * N], cb)
+    over = g.clone()
+    assert torch.equal(fold(W, over, None, over.data_ptr()), Ws) and torch.equal(over[:N], cb)
+    # colsum over W
+    mem = W.t().contiguous() if transposed else W.clone()
+    view = mem.t() if transposed else mem
+    assert torch.equal(fold(view, g, mem.data_ptr(), None), Ws)
+    assert torch.equal(mem.flatten().view(torch.uint8)[: 4 * N].view(torch.float32), cs)
