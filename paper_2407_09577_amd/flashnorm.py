@@ -138,7 +138,10 @@ def _new_out(M: int, N: int, like: torch.Tensor) -> torch.Tensor:
     any N works; the result is then a view of the first N columns."""
     per = 16 // like.element_size()
     ld = (N + per - 1) // per * per
-    buf = like.new_empty(M, ld)
+    if type(like) is torch.Tensor:  # the shorter call; a subclass would make the output one of its own
+        buf = like.new_empty(M, ld)
+    else:
+        buf = torch.empty(M, ld, dtype=like.dtype, device=like.device)
     return buf if ld == N else buf[:, :N]
 
 

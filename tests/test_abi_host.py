@@ -379,3 +379,20 @@ def test_binding_pads_the_outputs_it_allocates(fnlib):
             assert tuple(y.shape) == (3, n) and y.dtype == dtype and y.stride(1) == 1
             assert y.stride(0) % per == 0 and y.stride(0) - n < per
             assert y.is_contiguous() == (n % per == 0)
+
+
+def test_binding_allocates_plain_tensors(fnlib):
+    # The output is a torch.Tensor whatever the activations' own class, and that class is not asked to make it.
+    import torch
+
+    class Tagged(torch.Tensor):
+        @classmethod
+        def __torch_function__(cls, func, types, args=(), kwargs=None):
+            if getattr(func, "__name__", "").startswith("new_"):
+                raise AssertionError("the activations' class was asked for the output")
+            return super().__torch_function__(func, types, args, kwargs or {})
+
+    for like in (torch.zeros(1).as_subclass(Tagged), torch.nn.Parameter(torch.zeros(1)), torch.zeros(1)):
+        for n in (4, 45):
+            y = fnlib._new_out(3, n, like)
+            assert type(y) is torch.Tensor and not y.requires_grad and y.dtype == torch.float32
