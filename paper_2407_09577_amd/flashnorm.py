@@ -120,7 +120,10 @@ def _ld(t: torch.Tensor) -> int:
 
 def _stream(stream):
     if stream is None:  # the current stream of the current device
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # not part of torch's interface: a build may lack them
+            stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

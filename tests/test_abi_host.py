@@ -396,3 +396,17 @@ def test_binding_allocates_plain_tensors(fnlib):
         for n in (4, 45):
             y = fnlib._new_out(3, n, like)
             assert type(y) is torch.Tensor and not y.requires_grad and y.dtype == torch.float32
+
+
+def test_binding_asks_the_public_stream_where_torch_has_no_raw_one(fnlib, monkeypatch):
+    # The raw query is torch's own shortcut, not part of its interface: without it the stream comes from
+    # torch.cuda.current_stream().
+    import torch
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert fnlib._stream(None) == 0x1234
+    assert fnlib._stream(Stream()) == 0x1234 and fnlib._stream(77) == 77
