@@ -31,14 +31,35 @@ def _err(y, ref):
     return float(np.max(np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)))
 
 
-# 33 tiles of 16 x 64 and 32 (the few-row kernel), 128 and 127, 384 and 383 tiles of 32 rows; K below one
-# block and off every step; ragged rows and columns; one and two rows of wide outputs.
-SHAPES = [(16, 4, 33 * 64), (16, 36, 32 * 64), (3, 60, 4099), (1, 132, 65 * 64), (2, 64, 64 * 64), (129, 20, 1000),
-          (512, 516, 250), (509, 100, 260), (768, 1028, 1020), (737, 12, 1024), (31, 2048, 777), (250, 4092, 333)]
+# The kernel of a linear call by the documented rule, from its 16 x 64 and 32 x 64 tiles.
+def _kernel(M, K, N):
+    nt = (N + 63) // 64
+    t16, t32 = nt * ((M + 15) // 16), nt * ((M + 31) // 32)
+    if t16 <= 32 or (M <= 2 and nt <= 64) or (N <= 16 and t16 <= 64 and K >= 256):
+        return "few rows", t16
+    return ("32 rows, 4 waves", t32) if t32 >= 384 else ("16 rows, 4 waves" if t16 >= 128 else "16 rows, 8 waves", t16)
+
+
+# Both sides of every line of the rule; K below one block and off every step; ragged rows and columns; one and
+# two rows of wide outputs.
+SHAPES = {(16, 36, 32 * 64): ("few rows", 32), (16, 4, 33 * 64): ("16 rows, 8 waves", 33),
+          (16, 20, 127 * 64): ("16 rows, 8 waves", 127), (16, 20, 128 * 64): ("16 rows, 4 waves", 128),
+          (32, 12, 383 * 64): ("16 rows, 4 waves", 766), (32, 12, 384 * 64): ("32 rows, 4 waves", 384),
+          (2, 64, 64 * 64): ("few rows", 64), (1, 132, 65 * 64): ("16 rows, 8 waves", 65),
+          (3, 60, 4099): ("16 rows, 8 waves", 65), (129, 20, 1000): ("16 rows, 4 waves", 144),
+          (512, 516, 250): ("16 rows, 4 waves", 128), (509, 100, 260): ("16 rows, 4 waves", 160),
+          (768, 1028, 1020): ("32 rows, 4 waves", 384), (737, 12, 1024): ("32 rows, 4 waves", 384),
+          (47, 2048, 777): ("16 rows, 8 waves", 39), (250, 4092, 333): ("16 rows, 8 waves", 96),
+          (1024, 256, 16): ("few rows", 64), (1025, 256, 16): ("16 rows, 8 waves", 65),
+          (1024, 252, 16): ("16 rows, 8 waves", 64), (1024, 256, 17): ("16 rows, 8 waves", 64)}
+
+
+def test_shapes_hold_both_sides_of_the_rule():
+    assert {d: _kernel(*d) for d in SHAPES} == SHAPES
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("M,K,N", list(SHAPES))
 def test_parity_at_edges(M, K, N):
     from paper_2407_09577_amd import flashnorm as fn
     dev = "cuda:0"
@@ -158,3 +179,51 @@ def test_more_row_tiles_than_a_grid_dimension():
     n = h / (1e-5 + h.square().mean(2, keepdim=True)).sqrt()
     y = fn.flashnorm_qkv_headnorm(a, Ws, 1, 1, 8, 1e-5, one, one, one, 1e-5)
     assert err(y, n.flatten(1)) <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N", [(40, 1024), (1000, 1024)])  # 16-row and 32-row tiles
+def test_subnormals(M, N):
+    # Subnormal activations, weights, sums and results are kept: small integers times powers of two, whose products
+    # and sums are exact in fp32 (the few-row kernel's too).
+    from paper_2407_09577_amd import flashnorm as fn
+    K = 64
+    gen = torch.Generator().manual_seed(N)
+    ones = torch.ones(M, device="cuda")
+    for ea, ew in ((-149, 100), (100, -149), (-75, -70), (-140, 0)):
+        a = torch.ldexp(torch.randint(-7, 8, (M, K), generator=gen).double(), torch.tensor(ea))
+        W = torch.ldexp(torch.randint(-7, 8, (K, N), generator=gen).double(), torch.tensor(ew))
+        want = (a @ W).float()
+        assert torch.equal(want.double(), a @ W) and bool(want.any())
+        Wp = fn.fold_weights(W.float().cuda(), None)[0]
+        assert torch.equal(fn.rowscale_linear(a.float().cuda(), Wp, N, ones).cpu(), want), (ea, ew)
+        few = fn.rowscale_linear(a[:16, :].float().cuda(), fn.fold_weights(W[:, :64].float().cuda(), None)[0], 64, ones[:16])
+        assert torch.equal(few.cpu(), want[:16, :64]), (ea, ew)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(40, 200, 1000), (130, 1028, 1000), (800, 68, 1020)])
+def test_nonfinite_rows_stay_in_their_row(M, K, N):
+    # As the oracle: a row with NaN or an infinity is NaN throughout, every other row keeps its bits.
+    from paper_2407_09577_amd import flashnorm as fn
+    for kind in ("linear", "glu", "layernorm"):
+        w = workloads.make(kind, M, K, N // 2 if kind == "glu" else N, dtype=torch.float32, eps=1e-5, seed=M,
+                           a_mean=0.5 if kind == "layernorm" else 0.0)
+        bad = {0: float("inf"), 18: float("nan"), M - 1: float("-inf")}
+        ruined = w.a.clone()
+        for r, v in bad.items():
+            ruined[r, (5 * r) % K] = v
+        ln = kind == "layernorm"
+        Ws, cs, cb = fn.fold_weights(w.W.cuda(), w.g.cuda(), w.beta.cuda() if ln else None, colsum=ln, c_star=ln,
+                                     layout=fn.FN_LAYOUT_GLU if kind == "glu" else fn.FN_LAYOUT_LINEAR)
+
+        def run(a):
+            if ln:
+                return fn.flashnorm_layernorm_linear(a.cuda(), Ws, cs, cb, N, w.eps)
+            return (fn.flashnorm_glu(a.cuda(), Ws, N // 2, w.eps) if kind == "glu"
+                    else fn.flashnorm_linear(a.cuda(), Ws, N, w.eps))
+
+        clean, got = run(w.a), run(ruined)
+        good = torch.tensor([r not in bad for r in range(M)], device="cuda")
+        assert bool(torch.isnan(got[~good]).all()), kind
+        assert bool(torch.isfinite(clean).all()) and torch.equal(got[good], clean[good]), kind

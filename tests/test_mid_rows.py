@@ -1,7 +1,11 @@
-"""Middle-row kernel (csrc/mid_kernel.h): its register use on the CPU, and on the GPU every kind at the
-edges of its tiles (row blocks and groups, ragged columns and K, the smallest and the largest of its
-range) against the fp64 oracle, with the row error bar of the other bf16 paths."""
+"""Middle-row kernel (csrc/mid_kernel.h): its register use and the choice of its workgroup shape on the CPU; on
+the GPU the main kinds at the edges of its tiles (row blocks and groups, ragged columns and K, the smallest and
+the largest of its range) against the fp64 oracle, and every kind on every workgroup shape against fp64 products
+on the GPU, with the row error bar of the other bf16 paths."""
 import ctypes
+import glob
+import os
+import re
 
 import numpy as np
 import pytest
@@ -14,11 +18,23 @@ from paper_2407_09577_amd import workloads
 TOL = 2e-2  # row-normwise, bf16: one rounding of W* and one of the output (2 x 2^-8) and the fp32 sums
 
 
-@pytest.mark.parametrize("source", ["mid_kinds_a.hip", "mid_kinds_b.hip", "mid_kinds_c.hip"])
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2407_09577_amd", "csrc")
+KIND_SOURCES = sorted(os.path.basename(f) for f in glob.glob(os.path.join(CSRC, "mid_kinds_*.hip")))
+
+
+def test_every_kind_has_its_instances():
+    text = "".join(open(os.path.join(CSRC, f)).read() for f in KIND_SOURCES)
+    assert sorted(re.findall(r"launch_mid_epi<(EPI_\w+)>", text)) == sorted(
+        f"EPI_{k}" for k in ("RMS", "GLU", "LN", "NONE", "GLU_NOSCALE", "REGLU", "BILINEAR", "GLU_DEFER", "RELU_DEFER",
+                             "ROWSCALE", "ROPE"))
+
+
+@pytest.mark.parametrize("source", KIND_SOURCES)
 def test_no_spills(source, tmp_path):
     res = kernel_resources(source, tmp_path)
     assert res
-    assert [n for n, f in res.items() if f.get("private_segment_fixed_size", 0) or f.get("vgpr_spill_count", 0)] == []
+    assert [n for n, f in res.items() if f.get("private_segment_fixed_size", 0) or f.get("vgpr_spill_count", 0)
+            or f.get("sgpr_spill_count", 0)] == []
 
 
 def _shape(M, K, N, glu=False):
@@ -53,6 +69,29 @@ def _err(y, ref):
     got = y.float().cpu().double().numpy()
     assert np.isfinite(got).all()
     return float(np.max(np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)))
+
+
+# A call that each workgroup shape takes, plain (M, K, N) and GLU (M, K, 2 F): several row groups with a ragged
+# last one, a ragged last column tile, K off the 64-deep packing.  The non-temporal shapes take one group and
+# 96 MB of weights; shape 17 takes no GLU, and shape 11 is taken by GLUs alone.
+SHAPE_CALLS = [
+    (0, (35, 40, 257), (59, 40, 258)), (1, (65, 40, 2744), (66, 40, 2756)), (2, (65, 40, 5572), (65, 40, 5572)),
+    (3, (133, 112, 1638), (134, 112, 1682)), (4, (1394, 72, 485), (1393, 72, 482)), (5, (65, 40, 8316), (66, 40, 8198)),
+    (6, (1407, 1752, 333), (1397, 1944, 322)), (7, (98, 160, 8191), (97, 200, 8168)),
+    (8, (101, 1040, 8225), (99, 1048, 8244)), (9, (130, 656, 11416), (129, 552, 11124)),
+    (10, (535, 72, 26516), (522, 72, 26362)), (11, None, (198, 5224, 8250)), (12, (521, 40, 21781), (517, 40, 22188)),
+    (13, (30, 2888, 16613), (31, 2480, 19332)), (14, (34, 2152, 22315), (33, 2600, 18440)),
+    (15, (55, 2520, 19063), (59, 2768, 17350)), (16, (98, 40, 8195), (97, 40, 8268)), (17, (131, 520, 16863), None)]
+
+
+def test_every_shape_has_its_calls():
+    assert [c[0] for c in SHAPE_CALLS] == list(range(18))
+    for shape, plain, glu in SHAPE_CALLS:
+        if plain:
+            assert _shape(*plain) == shape, plain
+            assert _shape(*plain[:2], plain[2] // 4 * 4) == shape, plain  # the width that RoPE takes
+        if glu:
+            assert _shape(*glu, True) == shape, glu
 
 
 # (M, K, N): one row over the decode range, one over and under whole row blocks, several row groups,
@@ -140,3 +179,121 @@ def test_prefill_names_the_tile_kernel(M):
     ones = torch.ones(M, device="cuda")
     z = fn.flashnorm_linear_relu(a, Ws, N, w.eps, s, path=fn.FN_PATH_PREFILL)
     assert torch.equal(z, fn.rowscale_linear(a, Ws, N, ones, path=fn.FN_PATH_PREFILL).clamp(min=0))
+
+
+class _Call:
+    """Seeded operands on the GPU (activations in rows padded with NaN), and fp64 products of them."""
+
+    def __init__(self, M, K, N, glu, mean=0.0):
+        gen = torch.Generator(device="cuda").manual_seed(M + K + N)
+        a = (torch.randn(M, K, generator=gen, device="cuda") + mean).to(torch.bfloat16)
+        big = torch.full((M, K + 24), float("nan"), dtype=torch.bfloat16, device="cuda")
+        big[:, :K] = a
+        self.a, self.g = big[:, :K], torch.rand(K, generator=gen, device="cuda") + 0.5
+        self.W = (torch.randn(K, N, generator=gen, device="cuda") * K ** -0.5).to(torch.bfloat16)
+        self.beta = torch.randn(K, generator=gen, device="cuda") * 0.3
+        self.M, self.N, self.eps = M, N, 1e-5
+        self.x = a.double()
+        self.t = (self.x * self.g.double()) @ self.W.double()
+        self.s = (self.eps + self.x.square().mean(1, keepdim=True)).rsqrt()
+        self.layout = 1 if glu else 0
+        self.inv = torch.full((M,), float("nan"), device="cuda")
+
+    def pack(self, g=True, **kw):
+        from paper_2407_09577_amd import flashnorm as fn
+        return fn.fold_weights(self.W, self.g if g else None, layout=self.layout, **kw)
+
+    def check_inv(self):
+        assert float((self.inv.double() / self.s[:, 0] - 1).abs().max()) <= 1e-5
+
+
+def _row_err(y, ref):
+    assert y.shape == ref.shape and bool(torch.isfinite(y).all())
+    return float(((y.double() - ref).abs().amax(1) / ref.abs().amax(1)).max())
+
+
+def _rotate(v, pos, cos, sin):
+    p = v.reshape(v.shape[0], -1, cos.shape[1], 2)
+    c, s = cos.double()[pos.long()][:, None], sin.double()[pos.long()][:, None]
+    return torch.stack((p[..., 0] * c - p[..., 1] * s, p[..., 0] * s + p[..., 1] * c), -1).flatten(1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,dims", [(s, d) for s, d, _ in SHAPE_CALLS if d])
+def test_plain_kinds_on_every_shape(shape, dims):
+    from paper_2407_09577_amd import flashnorm as fn
+    M, K, N = dims
+    assert _shape(M, K, N) == shape
+    c = _Call(M, K, N, False)
+    Ws = c.pack()[0]
+    bias = torch.randn(N, device="cuda")
+    assert _row_err(fn.flashnorm_linear(c.a, Ws, N, c.eps, bias=bias, inv_rms=c.inv), c.t * c.s + bias.double()) <= TOL
+    c.check_inv()
+    c.inv.fill_(float("nan"))
+    assert _row_err(fn.flashnorm_linear_relu(c.a, Ws, N, c.eps, c.inv), c.t.clamp(min=0)) <= TOL
+    c.check_inv()
+    assert _row_err(fn.rowscale_linear(c.a, Ws, N, c.s[:, 0].float()), c.t * c.s) <= TOL
+    assert _row_err(fn.baseline_rmsnorm_linear(c.a, c.g, c.pack(g=False)[0], N, c.eps), c.t * c.s) <= TOL
+    c = _Call(M, K, N, False, mean=0.5)
+    Wl, cs, cb = c.pack(beta=c.beta, colsum=True, c_star=True)
+    d = c.x - c.x.mean(1, keepdim=True)
+    d = d / (d.square().mean(1, keepdim=True) + c.eps).sqrt() * c.g.double() + c.beta.double()
+    assert _row_err(fn.flashnorm_layernorm_linear(c.a, Wl, cs, cb, N, c.eps), d @ c.W.double()) <= TOL
+    heads = N // 4
+    c = _Call(M, K, 4 * heads, False)
+    Hkv = heads // 5
+    Hq = heads - 2 * Hkv
+    cos, sin = (v.cuda() for v in workloads.rope_tables(64, 4))
+    pos = torch.arange(M, device="cuda", dtype=torch.int32) % 64
+    qk = (Hq + Hkv) * 4
+    want = torch.cat((_rotate((c.t * c.s)[:, :qk], pos, cos, sin), (c.t * c.s)[:, qk:]), 1)
+    want[:, : Hq * 4] *= 0.5
+    y = fn.flashnorm_qkv_rope(c.a, c.pack()[0], Hq, Hkv, 4, c.eps, pos, cos, sin, 0.5, inv_rms=c.inv)
+    assert _row_err(y, want) <= TOL
+    c.check_inv()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,dims", [(s, d) for s, _, d in SHAPE_CALLS if d])
+def test_glu_kinds_on_every_shape(shape, dims):
+    from paper_2407_09577_amd import flashnorm as fn
+    M, K, N = dims
+    F = N // 2
+    assert _shape(M, K, N, True) == shape
+    c = _Call(M, K, N, True)
+    Wg = c.pack()[0]
+    gate, up = c.t[:, :F], c.t[:, F:]
+    silu = (gate * c.s) * torch.sigmoid(gate * c.s)
+    assert _row_err(fn.flashnorm_glu(c.a, Wg, F, c.eps), silu * up * c.s) <= TOL
+    assert _row_err(fn.flashnorm_glu_act(c.a, Wg, F, c.eps, fn.FN_GLU_REGLU), gate.clamp(min=0) * up * c.s ** 2) <= TOL
+    assert _row_err(fn.flashnorm_glu_act(c.a, Wg, F, c.eps, fn.FN_GLU_BILINEAR), gate * up * c.s ** 2) <= TOL
+    y = fn.flashnorm_glu_act(c.a, Wg, F, c.eps, fn.FN_GLU_SWIGLU_DEFER_UP, inv_rms=c.inv)
+    assert _row_err(y, silu * up) <= TOL
+    c.check_inv()
+    assert _row_err(fn.baseline_rmsnorm_glu(c.a, c.g, c.pack(g=False)[0], F, c.eps), silu * up * c.s) <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [0, 7, 9, 12, 16, 17])
+def test_nonfinite_rows_stay_in_their_row(shape):
+    # Rows holding NaN or an infinity are NaN throughout (their mean square is not finite), every other row has the
+    # bits it has beside finite rows.
+    from paper_2407_09577_amd import flashnorm as fn
+    for glu, dims in ((False, SHAPE_CALLS[shape][1]), (True, SHAPE_CALLS[shape][2])):
+        if dims is None:
+            continue
+        M, K, N = dims
+        c = _Call(M, K, N, glu, mean=0.25)
+        bad = {1: float("nan"), 17: float("inf"), M - 1: float("-inf")}
+        ruined = c.a.clone()
+        for r, v in bad.items():
+            ruined[r, (7 * r) % K] = v
+        Ws, cs, cb = c.pack(beta=None if glu else c.beta, colsum=not glu, c_star=not glu)
+        calls = [lambda a: fn.flashnorm_glu(a, Ws, N // 2, c.eps)] if glu else [
+            lambda a: fn.flashnorm_linear(a, Ws, N, c.eps),
+            lambda a: fn.flashnorm_layernorm_linear(a, Ws, cs, cb, N, c.eps)]
+        good = torch.tensor([r not in bad for r in range(M)], device="cuda")
+        for call in calls:
+            clean, got = call(c.a), call(ruined)
+            assert bool(torch.isnan(got[~good]).all())
+            assert bool(torch.isfinite(clean).all()) and torch.equal(got[good], clean[good])
