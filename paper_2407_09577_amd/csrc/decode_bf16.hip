@@ -339,13 +339,15 @@ static hipError_t launch_decode_cfg(const DecodeArgs& p) {
 //                        workgroup at M = 1..16 on the Llama-7B SwiGLU shape)
 //   544 <= npb < 1088    4 blocks x 4 waves x 1
 //   272 <= npb < 544     2 blocks x 4 waves x 2
-//   npb < 272            2 blocks x 8 waves x 1
+//   npb < 272            2 blocks x 8 waves x 1 (GLU, run-time g; else 257..271 blocks)
 //   npb <= 256, no GLU   1 block x 8 waves x 2, loads cached: a compute unit has room for every
-//                        workgroup, and one block each puts twice as many to work, each with as
-//                        many bytes in flight (measured over 456 random shapes of 1..16 rows, K
-//                        512..8192: 15 to 24% less time than 2 x 8 x 1 at any width up to 256,
-//                        weights cached or not, the worst shape 4% more; 16 x 4096 -> 4096 11.0
-//                        -> 8.4 us, 4 x 6144 -> 689 10.9 -> 6.9; at 257..400 blocks it loses 8%)
+//   and no run-time g    workgroup, and one block each puts twice as many to work, each with as
+//                        many bytes in flight (16 x 4096 -> 4096 11.0 -> 8.4 us, 4 x 6144 -> 689
+//                        10.9 -> 6.9; timed alone, over 64..4096 columns, K 1024..8192 and 1..16
+//                        rows, 0.64 to 1.01 of 2 x 8 x 1's time with 600 MB of weights read in
+//                        turn and 0.35 to 0.98 with the same weights in every call; only below
+//                        that K more, 9% of 3 us at 64 columns, K 512; at 257..400 blocks it
+//                        loses 8%)
 // With run-time g the wide case takes 8 x 2 x 2 (M <= 8) or 2 x 1 x 4 (the g
 // loads want four blocks per set).
 template <int EPI, bool GS>

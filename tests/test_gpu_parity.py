@@ -1248,7 +1248,7 @@ def test_random_sweep(fn, block):
 @pytest.mark.parametrize("seed", [11, 12, 13])
 def test_random_shapes_fp32(fn, seed):
     # fp32 operands on ragged shapes drawn from a fixed seed, through the automatic choice
-    # (64-row tiles, 16 x 64 tiles, or the few-row kernel at 4, 8 or 16 columns), at 1e-5.
+    # (the matrix-core kernel, or the few-row kernel at 4, 8 or 16 columns), at 1e-5.
     rng = np.random.default_rng(seed)
     for _ in range(8):
         M = int(rng.choice([1, 3, 16, 17, 40, 100, 257, 700]))
@@ -1274,7 +1274,7 @@ def test_random_shapes_fp32(fn, seed):
                                                        (900, 64, 4, 3, 64, True, True)])
 def test_qkv_headnorm_fp32(fn, M, K, Hq, Hkv, h, with_gv, rope):
     # Few rows run the few-row kernel (64-column tiles with per-head norms); 900 rows make
-    # enough 64 x 64 tiles for the 64-row kernel.
+    # enough 16 x 64 tiles for the matrix-core kernel.
     N = (Hq + 2 * Hkv) * h
     w = workloads.make("linear", M, K, N, dtype=torch.float32, eps=1e-5, seed=171 + M + h)
     g = torch.Generator().manual_seed(h)
