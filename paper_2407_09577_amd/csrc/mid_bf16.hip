@@ -56,8 +56,9 @@ float estimate_us(float r, int K, float fix, float round, float fill) {
 // 100 MB in every call, 32 rows: 18.6 us, non-temporal 24.4).  Otherwise the shape of the least
 // estimated time, if that is below 0.9 of the tile kernel's: over the shapes of the fit the
 // rule takes 0.62 of the tiles' time (geometric mean; the best choice at each shape 0.60).  More
-// than 1536 rows are outside the fit, and outputs narrower than 256 packed columns keep the tiles'
-// one chain of sums over K (the automatic tile there is bitwise the forced one).
+// than 1536 rows and fewer than 256 packed columns were not in the fit's sample and keep the tiles,
+// though single shapes are faster there (2048 x 5120 -> 576: tiles 35.0 us, shape 8 25.3;
+// 4096 x 5120 -> 576: 42.6 and, shape 11, 42.2; 64 x 8192 -> 128: 43.4 and, shape 0, 12.8).
 //
 // Below the fit's least K the estimates miss what a call is made of: prologue, epilogue and the
 // output's stores.  A second round pays the fixed part again; so do the 12- and 16-block shapes at

@@ -118,12 +118,16 @@ def _ld(t: torch.Tensor) -> int:
     return s[0]
 
 
+# torch's own shortcuts, not part of its interface: a build may lack them.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:  # the current stream of the current device
-        try:
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-        except AttributeError:  # not part of torch's interface: a build may lack them
-            stream = torch.cuda.current_stream()
+        if _raw_stream and _raw_device:
+            return _raw_stream(_raw_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

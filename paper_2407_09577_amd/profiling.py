@@ -27,13 +27,13 @@ PROFILES = os.path.join(ROOT, "profiles")
 
 
 def kernel_source(kernel: str) -> str:
-    """The csrc/*.hip file that defines the __global__ function ``kernel`` (a name such as
+    """The csrc/*.hip or *.h file that defines the __global__ function ``kernel`` (a name such as
     ``fn::f32_few_rows_kernel<...>`` or ``f32_few_rows_kernel``)."""
     base = re.split(r"[<(]", kernel)[0].split("::")[-1].split()[-1]
     if not base.endswith("_kernel"):
         raise ValueError(f"not a kernel name: {kernel}")
     pat = re.compile(r"__global__[^;{]*?\b" + re.escape(base) + r"\s*\(", re.S)
-    for src in sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip"))):
+    for src in sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")) + glob.glob(os.path.join(HERE, "csrc", "*.h"))):
         if pat.search(open(src).read()):
             return src
     raise ValueError(f"no source defines {base}")
@@ -110,8 +110,7 @@ def summarize(a) -> str:
         f"kernel: {name}",
         f"kernel_trace_calls: {calls}",
         f"kernel_avg_duration_us: {avg_ns / 1e3:.3f}  (all {calls} dispatches, warm-up included)",
-        f"kernel_timed_avg_duration_us: {timed_ns / 1e3:.3f}  (the last {a.timed_steps} dispatches: "
-        f"bench.py's last timed graph replay)",
+        f"kernel_timed_avg_duration_us: {timed_ns / 1e3:.3f}  (the last {a.timed_steps} dispatches: {a.timed_what})",
         f"fetch_size_kib_per_dispatch: {fetch_kib:.1f}  (mean of {nf} dispatches)",
         f"write_size_kib_per_dispatch: {write_kib:.1f}  (mean of {nw} dispatches)",
         f"copy_calibration: {a.copy_bytes} bytes copied; FETCH_SIZE {cal_fetch:.1f} KiB -> factor {f_fetch:.4f}; "
@@ -122,6 +121,11 @@ def summarize(a) -> str:
         f"mfma_busy_fraction: {util:.4f}  (SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE/{a.xcds} x {a.simds} SIMDs))",
         f"kernel_sources_sha256: {kernel_sources_sha256(a.kernel)}",
     ]
+    if a.lds:
+        active, _ = counter_mean(a.lds, a.kernel, "SQ_LDS_IDX_ACTIVE")
+        conflict, _ = counter_mean(a.lds, a.kernel, "SQ_LDS_BANK_CONFLICT")
+        lines.insert(-1, f"lds_bank_conflict_fraction: {conflict / active if active else 0.0:.4f}  "
+                         f"(SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE)")
     return "\n".join(lines) + "\n"
 
 
@@ -149,6 +153,8 @@ def main():
     for k in ("fetch", "write", "mfma", "cal-fetch", "cal-write"):
         p.add_argument(f"--{k}", required=True)
     p.add_argument("--trace", default=None, help="--kernel-trace --stats output of the same command")
+    p.add_argument("--lds", default=None, help="--pmc SQ_LDS_IDX_ACTIVE SQ_LDS_BANK_CONFLICT output")
+    p.add_argument("--timed-what", default="bench.py's last timed graph replay")
     p.add_argument("--copy-bytes", type=int, required=True)
     p.add_argument("--timed-steps", type=int, default=100, help="bench.py --steps of the traced command")
     p.add_argument("--xcds", type=int, default=8)

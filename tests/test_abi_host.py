@@ -406,7 +406,7 @@ def test_binding_asks_the_public_stream_where_torch_has_no_raw_one(fnlib, monkey
     class Stream:
         cuda_stream = 0x1234
 
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(fnlib, "_raw_stream", None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
     assert fnlib._stream(None) == 0x1234
     assert fnlib._stream(Stream()) == 0x1234 and fnlib._stream(77) == 77

@@ -27,3 +27,12 @@ def test_bench_defaults_to_the_largest_single_gpu_workload():
                  "mla_kv_down"):
         assert name in r.stdout
     assert "default workload is the largest single-GPU configuration" in r.stdout.replace("\n", " ")
+
+
+def test_profiles_find_every_kernel_source():
+    # The summaries hash the file that defines a kernel, header or not.
+    from paper_2407_09577_amd import profiling
+    for kernel, name in (("mid_bf16_kernel", "mid_kernel.h"), ("f32_mfma_kernel", "f32.hip"),
+                         ("fn::fold_sums_kernel<float, 0>", "fold.hip"), ("prefill_bf16_kernel", "prefill_bf16.hip")):
+        assert os.path.basename(profiling.kernel_source(kernel)) == name
+        assert len(profiling.kernel_sources_sha256(kernel)) == 64
