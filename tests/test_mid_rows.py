@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import __graft_entry__ as graft
 import oracle
 from _codeobj import kernel_resources
 from paper_2407_09577_amd import workloads
@@ -40,6 +41,7 @@ def test_no_spills(source, tmp_path):
 def _shape(M, K, N, glu=False):
     """The workgroup shape that the built library takes for a call (-1: the tile kernel)."""
     from paper_2407_09577_amd import flashnorm as fn
+    graft.ensure_built()
     choose = getattr(fn.lib(), "_ZN2fn9mid_shapeEiiib")
     choose.argtypes, choose.restype = [ctypes.c_int] * 3 + [ctypes.c_bool], ctypes.c_int
     return choose(M, K, 2 * ((N // 2 + 15) // 16 * 16) if glu else (N + 15) // 16 * 16, glu)
